@@ -73,42 +73,92 @@ S3A_HD Sim3d sim3_inverse(const Sim3d& a) {
   return r;
 }
 
+// 1 / sqrt(d) for d > 0. On the device the hardware estimate and two Newton steps
+// (relative error near 1e-16): a square root and a division each expand to a
+// longer chain of dependent FP64 operations.
+S3A_HD double rsqrt_pos(double d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double r = __builtin_amdgcn_rsq(d);
+  if (!(d > 1e-290 && d < 1e290)) return 1.0 / sqrt(d);  // where the steps would over- or underflow
+  const double h = -0.5 * d;
+  r = r * fma(h * r, r, 1.5);
+  r = r * fma(h * r, r, 1.5);
+  return r;
+#else
+  return 1.0 / sqrt(d);
+#endif
+}
+
+// The rotation of a Jacobi step on (app, apq; apq, aqq), apq != 0: t = tan of the
+// smaller angle, c and s its cosine and sine. t = 2 apq / (d + sign(d) |(d, 2 apq)|),
+// d = aqq - app, by reciprocal square roots where the squares stay in range.
+S3A_HD void jacobi_rotation(double app, double aqq, double apq, double& t, double& c, double& s) {
+  const double d = aqq - app, o = 2.0 * apq;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double h2 = d * d + o * o;
+  if (h2 > 1e-280 && h2 < 1e280) {
+    const double h = h2 * rsqrt_pos(h2);
+    const double den = d + (d >= 0.0 ? h : -h);
+    double r = __builtin_amdgcn_rcp(den);
+    r = r * fma(-den, r, 2.0);
+    r = r * fma(-den, r, 2.0);
+    t = o * r;
+    c = rsqrt_pos(fma(t, t, 1.0));
+    s = t * c;
+    return;
+  }
+#endif
+  const double theta = d / o;
+  t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+  c = 1.0 / sqrt(t * t + 1.0);
+  s = t * c;
+}
+
 // Cyclic Jacobi eigen-decomposition of a symmetric N x N matrix (row-major, in
-// place). On return A's diagonal holds the eigenvalues and the columns of V the
-// eigenvectors. Unsorted.
+// place; only its upper triangle is kept up). On return A's diagonal holds the
+// eigenvalues and the columns of V the eigenvectors. Unsorted. A sweep's
+// rotations come in rounds of disjoint pairs (N = 4: (0,1) (2,3), (0,2) (1,3),
+// (0,3) (1,2)), whose chains of dependent operations overlap in one lane.
 template <int N>
 S3A_HD void jacobi_eig(double* A, double* V) {
+  static_assert(N == 3 || N == 4, "pair order");
+  constexpr int PAIRS = N * (N - 1) / 2;
+  constexpr int P[6] = {0, N == 4 ? 2 : 0, N == 4 ? 0 : 1, 1, 0, 1};
+  constexpr int Q[6] = {1, N == 4 ? 3 : 2, 2, 3, 3, 2};
+  S3A_UNROLL
   for (int i = 0; i < N * N; ++i) V[i] = (i % (N + 1) == 0) ? 1.0 : 0.0;
+  S3A_NO_UNROLL
   for (int sweep = 0; sweep < 30; ++sweep) {
     double off = 0.0, diag = 0.0;
+    S3A_UNROLL
     for (int i = 0; i < N; ++i) {
       diag += A[i * N + i] * A[i * N + i];
+      S3A_UNROLL
       for (int j = i + 1; j < N; ++j) off += A[i * N + j] * A[i * N + j];
     }
     if (off <= 1e-34 * diag || off == 0.0) break;
-    for (int p = 0; p < N - 1; ++p) {
-      for (int q = p + 1; q < N; ++q) {
-        const double apq = A[p * N + q];
-        if (apq == 0.0) continue;
-        const double app = A[p * N + p], aqq = A[q * N + q];
-        const double theta = (aqq - app) / (2.0 * apq);
-        const double tt = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        const double c = 1.0 / sqrt(tt * tt + 1.0), s = tt * c;
-        for (int k = 0; k < N; ++k) {  // A <- A J (columns p, q)
-          const double akp = A[k * N + p], akq = A[k * N + q];
-          A[k * N + p] = c * akp - s * akq;
-          A[k * N + q] = s * akp + c * akq;
+    S3A_UNROLL
+    for (int x = 0; x < PAIRS; ++x) {
+      const int p = P[x], q = Q[x];
+      const double apq = A[p * N + q];
+      if (apq == 0.0) continue;
+      double t, c, s;
+      jacobi_rotation(A[p * N + p], A[q * N + q], apq, t, c, s);
+      A[p * N + p] -= t * apq;
+      A[q * N + q] += t * apq;
+      A[p * N + q] = 0.0;
+      S3A_UNROLL
+      for (int k = 0; k < N; ++k) {
+        if (k != p && k != q) {
+          double& kp = A[k < p ? k * N + p : p * N + k];
+          double& kq = A[k < q ? k * N + q : q * N + k];
+          const double akp = kp, akq = kq;
+          kp = c * akp - s * akq;
+          kq = s * akp + c * akq;
         }
-        for (int k = 0; k < N; ++k) {  // A <- J^T A (rows p, q)
-          const double apk = A[p * N + k], aqk = A[q * N + k];
-          A[p * N + k] = c * apk - s * aqk;
-          A[q * N + k] = s * apk + c * aqk;
-        }
-        for (int k = 0; k < N; ++k) {
-          const double vkp = V[k * N + p], vkq = V[k * N + q];
-          V[k * N + p] = c * vkp - s * vkq;
-          V[k * N + q] = s * vkp + c * vkq;
-        }
+        const double vkp = V[k * N + p], vkq = V[k * N + q];
+        V[k * N + p] = c * vkp - s * vkq;
+        V[k * N + q] = s * vkp + c * vkq;
       }
     }
   }
@@ -126,10 +176,16 @@ S3A_HD void rotation_from_cross_cov(const double* M, double* R) {
       M[3] - M[1], M[2] + M[6], M[5] + M[7], -M[0] - M[4] + M[8]};
   double V[16];
   jacobi_eig<4>(N, V);
-  int best = 0;
-  for (int i = 1; i < 4; ++i)
-    if (N[i * 5] > N[best * 5]) best = i;
-  double q0 = V[best], q1 = V[4 + best], q2 = V[8 + best], q3 = V[12 + best];
+  double best = N[0], q0 = V[0], q1 = V[4], q2 = V[8], q3 = V[12];
+  S3A_UNROLL
+  for (int i = 1; i < 4; ++i) {
+    const bool more = N[i * 5] > best;
+    best = more ? N[i * 5] : best;
+    q0 = more ? V[i] : q0;
+    q1 = more ? V[4 + i] : q1;
+    q2 = more ? V[8 + i] : q2;
+    q3 = more ? V[12 + i] : q3;
+  }
   const double n = sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
   q0 /= n; q1 /= n; q2 /= n; q3 /= n;
   R[0] = q0 * q0 + q1 * q1 - q2 * q2 - q3 * q3;
@@ -158,6 +214,19 @@ S3A_HD void singular_values3(const double* M, double* sv) {
   for (int i = 0; i < 3; ++i) sv[i] = sqrt(e[i] > 0.0 ? e[i] : 0.0);
 }
 
+// Whether the second singular value of M is clear of 1e-5 of the first, without
+// finding them: with l1 >= l2 >= l3 the eigenvalues of M^T M, the sum of its
+// principal 2 x 2 minors e2 = l1 l2 + l1 l3 + l2 l3 is at most 3 l1 l2, so
+// e2 > 3e-6 tr^2 gives l2 > 1e-6 l1, four decades above the test's 1e-10.
+S3A_HD bool second_singular_clear(const double* M) {
+  double A[9];
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j) A[3 * i + j] = M[i] * M[j] + M[3 + i] * M[3 + j] + M[6 + i] * M[6 + j];
+  const double tr = A[0] + A[4] + A[8];
+  const double e2 = (A[0] * A[4] - A[1] * A[1]) + (A[0] * A[8] - A[2] * A[2]) + (A[4] * A[8] - A[5] * A[5]);
+  return e2 > 3e-6 * tr * tr && e2 < 1e300;
+}
+
 enum { UMEYAMA_OK = 0, UMEYAMA_EMPTY = 1, UMEYAMA_DEGENERATE = 2 };
 
 // Weighted Umeyama from raw weighted moments (Sec. III-C.2, eq. (sim3)):
@@ -178,9 +247,11 @@ S3A_HD int umeyama_from_moments(double W, const double* sp, const double* sq, do
   double M[9];
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) M[3 * a + b] = sqp[3 * a + b] / W - mq[a] * mp[b];
-  double sv[3];
-  singular_values3(M, sv);
-  if (!(sv[1] > 1e-5 * sv[0])) return UMEYAMA_DEGENERATE;
+  if (!second_singular_clear(M)) {
+    double sv[3];
+    singular_values3(M, sv);
+    if (!(sv[1] > 1e-5 * sv[0])) return UMEYAMA_DEGENERATE;
+  }
   double R[9];
   rotation_from_cross_cov(M, R);
   double tr = 0.0;
@@ -227,37 +298,40 @@ S3A_HD bool cholesky_solve(double* H, const double* b, double* x) {
 
 // Cholesky solve of the SPD system H x = b with H given as its packed lower
 // triangle (row i holds H[i][0..i], at offset i (i + 1) / 2), overwritten by
-// the factor. Returns false when a pivot is not positive.
+// the factor (its diagonal as reciprocals). Right-looking: a column's scaling and
+// the update of the columns behind it are independent operations, so one lane's
+// chain per column is the reciprocal square root, one product and one update; y
+// is solved along with the factor. Returns false when a pivot is not positive.
 template <int N>
 S3A_HD bool cholesky_solve_packed(double* L, const double* b, double* x) {
+  bool ok = true;
+  double y[N];
+  S3A_UNROLL
+  for (int i = 0; i < N; ++i) y[i] = b[i];
+  S3A_UNROLL
   for (int j = 0; j < N; ++j) {
-    const int rj = j * (j + 1) / 2;
-    double d = L[rj + j];
-    for (int k = 0; k < j; ++k) d -= L[rj + k] * L[rj + k];
-    if (!(d > 0.0)) return false;
-    d = sqrt(d);
-    const double inv = 1.0 / d;
-    L[rj + j] = inv;  // the diagonal is kept as its reciprocal
+    const double d = L[j * (j + 1) / 2 + j];
+    ok = ok && d > 0.0;
+    const double inv = rsqrt_pos(ok ? d : 1.0);
+    L[j * (j + 1) / 2 + j] = inv;
+    y[j] *= inv;
+    S3A_UNROLL
+    for (int i = j + 1; i < N; ++i) L[i * (i + 1) / 2 + j] *= inv;
+    S3A_UNROLL
     for (int i = j + 1; i < N; ++i) {
-      const int ri = i * (i + 1) / 2;
-      double v = L[ri + j];
-      for (int k = 0; k < j; ++k) v -= L[ri + k] * L[rj + k];
-      L[ri + j] = v * inv;
+      const double lij = L[i * (i + 1) / 2 + j];
+      S3A_UNROLL
+      for (int k = j + 1; k <= i; ++k) L[i * (i + 1) / 2 + k] -= lij * L[k * (k + 1) / 2 + j];
+      y[i] -= lij * y[j];
     }
   }
-  double y[N];
-  for (int i = 0; i < N; ++i) {
-    const int ri = i * (i + 1) / 2;
-    double v = b[i];
-    for (int k = 0; k < i; ++k) v -= L[ri + k] * y[k];
-    y[i] = v * L[ri + i];
-  }
+  S3A_UNROLL
   for (int i = N - 1; i >= 0; --i) {
-    double v = y[i];
-    for (int k = i + 1; k < N; ++k) v -= L[k * (k + 1) / 2 + i] * x[k];
-    x[i] = v * L[i * (i + 1) / 2 + i];
+    x[i] = y[i] * L[i * (i + 1) / 2 + i];
+    S3A_UNROLL
+    for (int k = 0; k < i; ++k) y[k] -= L[i * (i + 1) / 2 + k] * x[i];
   }
-  return true;
+  return ok;
 }
 
 // F_n(sigma) = int_0^1 exp(sigma u) u^n du.
@@ -286,27 +360,39 @@ constexpr double inv_factorial(int n) {
 // Rotation R = exp([omega]_x) (Rodrigues) and the translation map
 // V = int_0^1 e^{sigma u} exp(u [omega]_x) du = a0 I + c1 [omega]_x + c2 [omega]_x^2,
 // a0 = F_0(sigma), c1 = int e^{sigma u} sin(u th)/th du,
-// c2 = int e^{sigma u} (1 - cos(u th))/th^2 du, th = |omega|.
-S3A_HD void sim3_RV(const double* w, double sg, double* R, double* V) {
+// c2 = int e^{sigma u} (1 - cos(u th))/th^2 du, th = |omega|. Returns e^sigma.
+S3A_HD double sim3_RV(const double* w, double sg, double* R, double* V) {
   const double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-  const double th = sqrt(th2);
   double A, B;  // Rodrigues coefficients sin(th)/th, (1 - cos th)/th^2
-  double c1, c2, a0;
-  if (th < 0.1 && fabs(sg) < 4.0) {
+  double c1, c2, a0, es;
+  if (th2 < 0.01 && fabs(sg) < 4.0) {
     // Expansion in th^2 with F_n(sigma) = int_0^1 e^{sigma u} u^n du:
     //   c1 = sum_m (-1)^m th^{2m} F_{2m+1} / (2m+1)!,  c2 = sum_m (-1)^m th^{2m} F_{2m+2} / (2m+2)!,
     //   a0 = F_0, and A, B the Taylor series of sin th / th and (1 - cos th) / th^2,
     // truncated after m = 4 (th^10 / 11! < 3e-18). The F_n come from the downward
-    // recurrence n F_{n-1} = e^sigma - sigma F_n started at n = 40 from
-    // F_40 ~ e^sigma / (41 + sigma): each step scales the start error by |sigma| / n,
-    // so below n = 10 it is under 1e-23 for |sigma| < 4. Horner in th^2 runs
-    // with the recurrence (m falls as n falls).
-    const double es = exp(sg);
-    double F = es / (41.0 + sg);
+    // recurrence F_{n-1} = (e^sigma - sigma F_n) / n, whose products with 1 / n do not
+    // depend on F (one fused operation per step on the chain), from
+    // F_N ~ e^sigma / (N + 1 + sigma) (relative error below |sigma| / N^2). Each step
+    // scales that error by |sigma| / n, and F_n enters with th^(n-1) / n! or less:
+    // N = 40 for |sigma| < 4, and N = 12 for |sigma| < 1/16 (a converging solve's
+    // steps), where F_9 is within 1e-10 at a weight of 3e-14 and F_7 within 1e-14;
+    // there e^sigma is its Taylor polynomial too (the next term is below 1e-23).
+    double F;
+    if (fabs(sg) < 0.0625) {
+      es = 1.0;
+      S3A_UNROLL
+      for (int n = 11; n >= 1; --n) es = es * (sg * (1.0 / n)) + 1.0;
+      F = es / (13.0 + sg);
+    } else {
+      es = exp(sg);
+      F = es / (41.0 + sg);
+      S3A_UNROLL
+      for (int n = 40; n > 12; --n) F = es * (1.0 / n) - (sg * (1.0 / n)) * F;
+    }
     c1 = 0.0; c2 = 0.0;
     S3A_UNROLL
-    for (int n = 40; n >= 1; --n) {
-      F = (es - sg * F) * (1.0 / n);  // F_{n-1}
+    for (int n = 12; n >= 1; --n) {
+      F = es * (1.0 / n) - (sg * (1.0 / n)) * F;  // F_{n-1}
       const int j = n - 1;
       if (j >= 1 && j <= 10) {
         const double coef = (((j - 1) / 2) & 1 ? -1.0 : 1.0) * inv_factorial(j);
@@ -322,7 +408,8 @@ S3A_HD void sim3_RV(const double* w, double sg, double* R, double* V) {
       A = A * th2 + sgn * inv_factorial(2 * m + 1);
       B = B * th2 + sgn * inv_factorial(2 * m + 2);
     }
-  } else if (th < 0.1) {
+  } else if (th2 < 0.01) {
+    es = exp(sg);
     a0 = int_exp_pow(0, sg);
     // series in th^2: sin(u th)/th = sum (-1)^k th^{2k} u^{2k+1}/(2k+1)!,
     // (1-cos(u th))/th^2 = sum (-1)^k th^{2k} u^{2k+2}/(2k+2)!
@@ -339,12 +426,13 @@ S3A_HD void sim3_RV(const double* w, double sg, double* R, double* V) {
       f2 *= (double)((2 * k + 3) * (2 * k + 4));
     }
   } else {
+    const double th = sqrt(th2);
     a0 = sg == 0.0 ? 1.0 : expm1(sg) / sg;
     const double sn = sin(th), cs = cos(th);
     A = sn / th;
     B = (1.0 - cs) / th2;
     const double den = sg * sg + th2;
-    const double es = exp(sg);
+    es = exp(sg);
     const double Is = (es * (sg * sn - th * cs) + th) / den;
     const double Ic = (es * (sg * cs + th * sn) - sg) / den;
     c1 = Is / th;
@@ -358,15 +446,15 @@ S3A_HD void sim3_RV(const double* w, double sg, double* R, double* V) {
     R[i] = I + A * Wm[i] + B * W2[i];
     V[i] = a0 * I + c1 * Wm[i] + c2 * W2[i];
   }
+  return es;
 }
 
 // Exp of xi = (rho, omega, sigma) = {e^sigma, exp([omega]_x), V rho}.
 S3A_HD Sim3d sim3_exp(const double* xi) {
   Sim3d r;
   double V[9];
-  sim3_RV(xi + 3, xi[6], r.R, V);
+  r.s = sim3_RV(xi + 3, xi[6], r.R, V);
   mat3_vec(V, xi, r.t);
-  r.s = exp(xi[6]);
   return r;
 }
 

@@ -24,10 +24,10 @@ __device__ inline Sim3d load_sim3(const s3a_sim3* o) {
 }
 
 __device__ inline bool sim3_finite(const Sim3d& S) {
-  bool f = __builtin_isfinite(S.s) && S.s > 0.0;
-  for (int i = 0; i < 9; ++i) f = f && __builtin_isfinite(S.R[i]);
-  for (int i = 0; i < 3; ++i) f = f && __builtin_isfinite(S.t[i]);
-  return f;
+  double z = S.s * 0.0;  // stays zero unless an entry is NaN or infinite
+  for (int i = 0; i < 9; ++i) z = fma(S.R[i], 0.0, z);
+  for (int i = 0; i < 3; ++i) z = fma(S.t[i], 0.0, z);
+  return z == 0.0 && S.s > 0.0;
 }
 
 __device__ inline void publish(PointParams* P, const Sim3d& S, const double* c, int active, int nonfinite = 1) {
@@ -88,14 +88,15 @@ __device__ inline void assemble_gn_packed(const double* st, double* L, double* g
   for (int i = 0; i < 7; ++i) g[i] = st[10 + i];
 }
 
-// Moments pass -> weighted Umeyama start (or the caller's), validity, centre.
-__device__ inline void finalize_moments(const Shape& sh, const CallDesc* cd, Work& w, int k, const PairSched& sc,
-                                        const double* s) {
+// Moments pass -> weighted Umeyama start (or the caller's), validity, centre: the
+// pair's state from its summed statistics. Returns whether passes follow.
+__device__ inline bool state_from_moments(const Shape& sh, const s3a_sim3* init, bool bad, const double* s,
+                                          PairState* st) {
   const double nan = __builtin_nan("");
-  PairState* st = w.state + k;
+  const int64_t V = (int64_t)s[17], nnf = (int64_t)s[18];
   st->C = s[0];
-  st->V = (int64_t)s[17];
-  st->nnf = (int64_t)s[18];
+  st->V = V;
+  st->nnf = nnf;
   st->cost_lin = nan;
   for (int i = 0; i < 28; ++i) st->H[i] = nan;
   for (int i = 0; i < 7; ++i) st->g[i] = nan;
@@ -104,16 +105,16 @@ __device__ inline void finalize_moments(const Shape& sh, const CallDesc* cd, Wor
   int status = S3A_PAIR_OK;
   double cq[3] = {0.0, 0.0, 0.0};
   Sim3d S = sim3_identity();
-  if (sc.bad) {
+  if (bad) {
     status = S3A_PAIR_BADRANGE;
-  } else if (st->V == 0) {
-    status = st->nnf > 0 ? S3A_PAIR_NONFINITE : S3A_PAIR_EMPTY;
+  } else if (V == 0) {
+    status = nnf > 0 ? S3A_PAIR_NONFINITE : S3A_PAIR_EMPTY;
   } else if (!(s[0] > 0.0)) {
     status = S3A_PAIR_DEGENERATE;
   } else {
     const int u = umeyama_from_moments(s[0], s + 1, s + 4, s[7], s + 8, &S, cq);
-    if (cd->init) {
-      S = load_sim3(cd->init + k);
+    if (init) {
+      S = load_sim3(init);
       if (!sim3_finite(S)) status = S3A_PAIR_NONFINITE;
     } else if (u != UMEYAMA_OK) {
       status = u == UMEYAMA_EMPTY ? S3A_PAIR_EMPTY : S3A_PAIR_DEGENERATE;
@@ -123,21 +124,18 @@ __device__ inline void finalize_moments(const Shape& sh, const CallDesc* cd, Wor
   st->S = S;
   for (int i = 0; i < 3; ++i) st->cq[i] = cq[i];
   st->status = status;
-  const bool more = status == S3A_PAIR_OK && (sh.K > 0 || (sh.flags & S3A_FLAG_FINAL_COST));
-  if (!more) write_outputs(cd, k, *st, nan, 0);
-  publish(w.params + k, S, cq, more ? 1 : 0, st->nnf > 0 ? 1 : 0);
+  return status == S3A_PAIR_OK && (sh.K > 0 || (sh.flags & S3A_FLAG_FINAL_COST));
 }
 
 // Gauss-Newton pass `pass` (1..K): assemble H, g in centred coordinates from the
 // 17 statistics, Cholesky solve, map the step back, S <- Exp(xi) S. The
 // reported H, g are those of the uncentred Jacobian, rebuilt from the same
-// statistics shifted back by the centre c (y = y_c + c).
-__device__ inline void finalize_gn(const Shape& sh, const CallDesc* cd, Work& w, int k, int pass, const double* s) {
-  PairState* st = w.state + k;
-  if (st->status != S3A_PAIR_OK || !w.params[k].active) return;
-  const double nan = __builtin_nan("");
+// statistics shifted back by the centre c (y = y_c + c). Returns whether passes
+// follow. The state is read at the start in one batch (its latency is paid once).
+__device__ inline bool state_from_gn(const Shape& sh, int pass, const double* s, PairState* st) {
   const double c[3] = {st->cq[0], st->cq[1], st->cq[2]};
   const double C = st->C;
+  const Sim3d S = st->S;
   st->cost_lin = s[17] / C;  // the cost and inlier count at the linearisation point
   st->inl_lin = (int64_t)s[18];
   double Hp[28], g[7], x[7];
@@ -151,7 +149,7 @@ __device__ inline void finalize_gn(const Shape& sh, const CallDesc* cd, Work& w,
     xi[1] = x[1] + (c[2] * x[3] - c[0] * x[5]) - x[6] * c[1];
     xi[2] = x[2] + (c[0] * x[4] - c[1] * x[3]) - x[6] * c[2];
     for (int i = 3; i < 7; ++i) xi[i] = x[i];
-    const Sim3d Snew = sim3_compose(sim3_exp(xi), st->S);
+    const Sim3d Snew = sim3_compose(sim3_exp(xi), S);
     if (!sim3_finite(Snew)) {
       status = S3A_PAIR_NONFINITE;
     } else {
@@ -187,11 +185,24 @@ __device__ inline void finalize_gn(const Shape& sh, const CallDesc* cd, Work& w,
     status = S3A_PAIR_DEGENERATE;
   }
   st->status = status;
-  const bool failed = status != S3A_PAIR_OK;
-  const bool last = pass == sh.K;
-  const bool final_pass = (sh.flags & S3A_FLAG_FINAL_COST) != 0;
-  if (failed || (last && !final_pass)) write_outputs(cd, k, *st, nan, 0);
-  publish(w.params + k, st->S, c, (failed || (last && !final_pass)) ? 0 : 1, st->nnf > 0 ? 1 : 0);
+  return status == S3A_PAIR_OK && (pass < sh.K || (sh.flags & S3A_FLAG_FINAL_COST) != 0);
+}
+
+// The same on the call's per-pair state and parameters in device memory.
+__device__ inline void finalize_moments(const Shape& sh, const CallDesc* cd, Work& w, int k, const PairSched& sc,
+                                        const double* s) {
+  PairState* st = w.state + k;
+  const bool more = state_from_moments(sh, cd->init ? cd->init + k : nullptr, sc.bad != 0, s, st);
+  if (!more) write_outputs(cd, k, *st, __builtin_nan(""), 0);
+  publish(w.params + k, st->S, st->cq, more ? 1 : 0, st->nnf > 0 ? 1 : 0);
+}
+
+__device__ inline void finalize_gn(const Shape& sh, const CallDesc* cd, Work& w, int k, int pass, const double* s) {
+  PairState* st = w.state + k;
+  if (st->status != S3A_PAIR_OK || !w.params[k].active) return;
+  const bool more = state_from_gn(sh, pass, s, st);
+  if (!more) write_outputs(cd, k, *st, __builtin_nan(""), 0);
+  publish(w.params + k, st->S, st->cq, more ? 1 : 0, st->nnf > 0 ? 1 : 0);
 }
 
 __device__ inline void finalize_final_cost(const CallDesc* cd, Work& w, int k, const double* s) {
