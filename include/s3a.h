@@ -32,8 +32,7 @@
  *     stream) and return; device outputs are valid once the stream has
  *     reached that point. Calls that say they synchronise do so on that
  *     stream before returning.
- *   - A handle owns its workspace (grown on demand), captured graphs and
- *     autotuning results. A handle must not be used by two threads at once.
+ *   - A handle owns its workspace (grown on demand) and autotuning results. A handle must not be used by two threads at once.
  *   - Calls through one handle share that workspace, so they execute in the
  *     order they were issued, whatever streams they are given: a call on a
  *     stream other than the previous call's makes its stream wait (on the
@@ -94,7 +93,7 @@ enum {
 /* Flags of s3a_align_desc.flags. */
 #define S3A_FLAG_PLAIN 0x1u        /* one pair at a time, one launch per pass */
 #define S3A_FLAG_FINAL_COST 0x2u   /* one more pass: cost and inliers at the final iterate */
-#define S3A_FLAG_NO_GRAPH 0x4u     /* batched: launch directly, do not capture/replay a graph */
+#define S3A_FLAG_NO_GRAPH 0x4u     /* accepted, changes nothing: every call launches its kernels directly */
 #define S3A_FLAG_PERSISTENT 0x8u   /* batched: one persistent launch for all passes (see s3a_align_pairs) */
 
 /*
@@ -147,8 +146,8 @@ int s3a_destroy(s3a_handle* h);
  *   S_out:  device, n_pairs results (the K-th Gauss-Newton iterate).
  *   info:   device, n_pairs diagnostics, or NULL.
  * Batched (default): all pairs together; each pass is one launch over every
- * tile of every pair plus one FP64 finalize launch, the whole sequence
- * captured once in a graph and replayed on later calls of the same shape.
+ * tile of every pair, followed by one FP64 finalize launch, or, in untuned calls
+ * of few tiles, solving the pass before itself.
  * S3A_FLAG_PERSISTENT: all passes in one persistent launch that hands out
  * (pass, tile) work items in pass-major order and finalizes each pair when
  * its last tile of a pass arrives (its per-item cross-workgroup release and
@@ -439,8 +438,7 @@ int s3a_set_tuning(s3a_handle* h, int32_t dtype, const s3a_tuning* t); /* t = NU
 int s3a_get_tuning(s3a_handle* h, int32_t dtype, int64_t n_points, s3a_tuning* t);
 
 /*
- * Kernel timing (profiling aid). While on, calls launch directly (no graph
- * replay) and record HIP events on the caller's stream around every launch of
+ * Kernel timing (profiling aid). While on, calls record HIP events on the caller's stream around every launch of
  * the call's dominant point kernel: the persistent kernel of a batched call,
  * the pass kernels of a plain or multi-launch call, the adjoint kernel of a
  * backward call, the cost kernel of a cost call. s3a_kernel_time synchronises

@@ -159,34 +159,41 @@ struct Planes<S3A_BF16> {
 // alternate: the next item's loads are issued before the current item is
 // worked on, so every wavefront keeps loads in flight while it computes.
 // fetch(rel, raw) issues the loads of the vector at rel; body(raw, rel0)
-// consumes one. ITEMS is even. A lane runs the items with rel0 < end_rel; with
-// UNIFORM, every lane runs every item that starts before end_rel for some lane
-// (end_rel is the same for the whole workgroup), so that the body may use
-// cross-lane operations, and masks elements at or past end_rel itself (the
-// fetch bounds-checks against the planes' end).
-template <int WG, int ITEMS, int VEC, typename Raw, bool UNIFORM = false, typename Fetch, typename Body>
-__device__ inline void pipelined_items(int end_rel, Fetch&& fetch, Body&& body) {
+// consumes one. ITEMS is even. A lane runs the items with rel0 < end_rel. BEGUN:
+// the caller has issued the first item's loads into A (pipelined_begin) some time
+// before, to cover other latency with them.
+template <int WG, int VEC, typename Raw, typename Fetch>
+__device__ inline void pipelined_begin(int end_rel, Fetch&& fetch, Raw& A) {
+  const int first = (int)threadIdx.x * VEC;
+  if (first < end_rel) fetch(first, A);
+}
+template <int WG, int ITEMS, int VEC, typename Raw, bool BEGUN, typename Fetch, typename Body>
+__device__ inline void pipelined_walk(int end_rel, Fetch&& fetch, Body&& body, Raw& A) {
   static_assert(ITEMS % 2 == 0, "items per lane must be even");
   constexpr int STRIDE = WG * VEC;
-  Raw A, B;
+  Raw B;
   const int first = (int)threadIdx.x * VEC;
-  if (UNIFORM ? end_rel <= 0 : first >= end_rel) return;
-  fetch(first, A);
+  if (first >= end_rel) return;
+  if constexpr (!BEGUN) fetch(first, A);
 #pragma unroll 1
   for (int it = 0; it < ITEMS; it += 2) {
-    const int base = it * STRIDE;
-    const int r0 = first + base;
+    const int r0 = first + it * STRIDE;
     const int r1 = r0 + STRIDE;
-    const bool more1 = UNIFORM ? base + STRIDE < end_rel : r1 < end_rel;
+    const bool more1 = r1 < end_rel;
     if (more1) fetch(r1, B);
     body(A, r0);
     if (!more1) break;
     const int r2 = r1 + STRIDE;
-    const bool more2 = it + 2 < ITEMS && (UNIFORM ? base + 2 * STRIDE < end_rel : r2 < end_rel);
+    const bool more2 = it + 2 < ITEMS && r2 < end_rel;
     if (more2) fetch(r2, A);
     body(B, r1);
     if (!more2) break;
   }
+}
+template <int WG, int ITEMS, int VEC, typename Raw, typename Fetch, typename Body>
+__device__ inline void pipelined_items(int end_rel, Fetch&& fetch, Body&& body) {
+  Raw A;
+  pipelined_walk<WG, ITEMS, VEC, Raw, false>(end_rel, fetch, body, A);
 }
 
 // Gradients are written once and not read back by the library: streaming
@@ -253,6 +260,8 @@ __device__ inline TileDesc load_tile(const TileDesc* p) {
   r.end = ((long long)(unsigned)uniform_i32((int)(e >> 32)) << 32) | (unsigned)uniform_i32((int)e);
   r.lo = ((long long)(unsigned)uniform_i32((int)(l >> 32)) << 32) | (unsigned)uniform_i32((int)l);
   r.pair = uniform_i32(p->pair);
+  r.tile0 = uniform_i32(p->tile0);
+  r.ntiles = uniform_i32(p->ntiles);
   r.pad = 0;
   return r;
 }
@@ -625,13 +634,40 @@ __device__ inline void gn_point(float (&a)[NSTAT], float y0, float y1, float y2,
   }
 }
 
+// The raw buffers of a tile's walk, whatever the input kind.
+template <int DT>
+struct TileRaw {
+  typedef RawVec type;
+};
+template <>
+struct TileRaw<DT_DEPTH_F32> {
+  typedef DepthPlanes<DT_DEPTH_F32>::Raw type;
+};
+template <>
+struct TileRaw<DT_DEPTH_BF16> {
+  typedef DepthPlanes<DT_DEPTH_BF16>::Raw type;
+};
+
+// Issue the loads of the lane's first vector of a tile.
+template <int DT, int WG>
+__device__ inline void tile_begin(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
+                                  typename TileRaw<DT>::type& r) {
+  using Raw = typename TileRaw<DT>::type;
+  if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
+    if (src.frame < 0) return;  // a tile that spans frames does not walk raw vectors
+  }
+  pipelined_begin<WG, Planes<DT>::VEC, Raw>(
+      (int)(td.end - td.begin), [&](int rel, Raw& x) { Planes<DT>::fetch(src, td.begin + rel, sh.n_points, x); }, r);
+}
+
 // Gauss-Newton pass over a depth tile that lies in one frame: the pair's
 // current similarity is folded into each side's camera once per tile, so a
 // pixel costs one affine map per side on its ray:
 //   y_c = d_p (A ray_p) + b,  A = sR R_p, b = sR t_p + t - c;   q_c = d_q (R_q ray_q) + t_q - c.
-template <int DT, int WG, int ITEMS, bool COST>
+template <int DT, int WG, int ITEMS, bool COST, bool BEGUN>
 __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
-                                           const PointParams& P, float (&a)[NSTAT]) {
+                                           const PointParams& P, typename DepthPlanes<DT>::Raw& first,
+                                           float (&a)[NSTAT]) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC;
   const DepthCam& cp = src.cp;
@@ -649,9 +685,8 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
   const bool check_finite = P.nonfinite != 0;
-  pipelined_items<WG, ITEMS, VEC, typename L::Raw>(
-      end_rel, [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); },
-      [&](const typename L::Raw& raw, int rel0) {
+  auto fetch = [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); };
+  auto body = [&](const typename L::Raw& raw, int rel0) {
     float d[3][VEC];
     L::unpack(raw, d);
     int f, row, col;
@@ -680,7 +715,8 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
       gn_point<COST>(a, y[0], y[1], y[2], y[0] - q[0], y[1] - q[1], y[2] - q[2], w, d2, delta, hd2);
       if (rel0 + e >= lo_rel) L::advance(src, f, row, col);
     }
-  });
+  };
+  pipelined_walk<WG, ITEMS, VEC, typename L::Raw, BEGUN>(end_rel, fetch, body, first);
 }
 
 
@@ -737,16 +773,16 @@ __device__ inline void gn_vector(const Shape& sh, const PointParams& P, RawVec& 
   }
 }
 
-template <int DT, int WG, int ITEMS, bool COST>
+template <int DT, int WG, int ITEMS, bool COST, bool BEGUN = false>
 __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td, const PointParams& P,
-                               double (*red)[NSTAT], double* out) {
+                               typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out) {
   constexpr int VEC = Planes<DT>::VEC;
   float a[NSTAT];
 #pragma unroll
   for (int j = 0; j < NSTAT; ++j) a[j] = 0.0f;
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
     if (P.active && pl.frame >= 0) {
-      tile_gn_depth_frame<DT, WG, ITEMS, COST>(sh, pl, td, P, a);
+      tile_gn_depth_frame<DT, WG, ITEMS, COST, BEGUN>(sh, pl, td, P, first, a);
       block_store_f32<WG>(a, red, out);
       return;
     }
@@ -755,9 +791,9 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
     const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
     const bool check_finite = P.nonfinite != 0;
     if constexpr (DT == S3A_F32 || DT == S3A_BF16) {
-      pipelined_items<WG, ITEMS, VEC, RawVec>(
-          end_rel, [&](int rel, RawVec& r) { Planes<DT>::fetch(pl, td.begin + rel, sh.n_points, r); },
-          [&](RawVec& r, int rel0) { gn_vector<DT, COST>(sh, P, r, rel0, lo_rel, end_rel, check_finite, a); });
+      auto fetch = [&](int rel, RawVec& r) { Planes<DT>::fetch(pl, td.begin + rel, sh.n_points, r); };
+      auto body = [&](RawVec& r, int rel0) { gn_vector<DT, COST>(sh, P, r, rel0, lo_rel, end_rel, check_finite, a); };
+      pipelined_walk<WG, ITEMS, VEC, RawVec, BEGUN>(end_rel, fetch, body, first);
     } else {
       // depth input whose tile spans frames: unprojected per element (DepthPlanes::load)
       const float tau = sh.tau, delta = sh.delta_f;
@@ -971,10 +1007,9 @@ __device__ inline void tile_cost(const Shape& sh, const SrcCtx<DT>& pl, const Ti
 template <int DT, int MODE, int WG, int ITEMS>
 __device__ inline void tile_body(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td,
                                  const PointParams& P, double (*red)[NSTAT], double* out) {
-  if constexpr (MODE == MODE_GN) {
-    tile_gn<DT, WG, ITEMS, true>(sh, pl, td, P, red, out);
-  } else if constexpr (MODE == MODE_GN_NC) {
-    tile_gn<DT, WG, ITEMS, false>(sh, pl, td, P, red, out);
+  if constexpr (MODE == MODE_GN || MODE == MODE_GN_NC) {
+    typename TileRaw<DT>::type first;
+    tile_gn<DT, WG, ITEMS, MODE == MODE_GN>(sh, pl, td, P, first, red, out);
   } else if constexpr (MODE == MODE_MOMENTS) {
     tile_moments<DT, WG, ITEMS>(sh, pl, td, red, out);
   } else {

@@ -18,14 +18,19 @@ inline int64_t tile_elems(int dtype, const LaunchCfg& lc) { return (int64_t)lc.w
 // Upper bound of the tile count of any batch (see k_sched).
 inline int64_t max_tiles(int64_t n_points, int n_pairs, int64_t tile) { return n_points / tile + 2 * (int64_t)n_pairs + 1; }
 
-hipError_t launch_sched(const Shape& sh, const CallDesc* cd, const Work& w, hipStream_t st);
+// The call's schedule (tile table, per-pair ranges, depth cameras in pass form; a
+// depth pair of invalid geometry is marked bad); stores the descriptor c to *cd.
+hipError_t launch_sched(const Shape& sh, const CallDesc& c, CallDesc* cd, const Work& w, hipStream_t st);
 hipError_t launch_pass(int dtype, int mode, const LaunchCfg& lc, const Shape& sh, const CallDesc* cd, const Work& w,
                        int32_t tile_lo, int32_t tile_hi, int grid, hipStream_t st);
-hipError_t launch_finalize(int kind, const Shape& sh, const CallDesc* cd, const Work& w, int pass, int32_t pair_lo,
-                           int32_t n, hipStream_t st);
+// A Gauss-Newton pass (>= 1) that solves the pass before it first, at the untuned
+// shapes (256 threads; 4 items FP32, 2 BF16, 16 depth), and the solve after the last.
+hipError_t launch_pass_solve(int dtype, const Shape& sh, const CallDesc* cd, const Work& w, int pass, int grid,
+                             hipStream_t st);
+hipError_t launch_solve_last(const Shape& sh, const CallDesc* cd, const Work& w, int pass, hipStream_t st);
+hipError_t launch_finalize(const Shape& sh, const CallDesc* cd, const Work& w, int pass, int32_t pair_lo, int32_t n,
+                           hipStream_t st);
 hipError_t launch_prep(const Shape& sh, const CallDesc* cd, const Work& w, int adjoint, hipStream_t st);
-// Depth input: per-pair cameras into pass form; invalid geometry marks the pair bad.
-hipError_t launch_depth_prep(const Shape& sh, const CallDesc* cd, const Work& w, hipStream_t st);
 hipError_t launch_finalize_cost(const Shape& sh, const CallDesc* cd, const Work& w, hipStream_t st);
 hipError_t launch_adjoint(int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* cd, const Work& w, int grid,
                           hipStream_t st);

@@ -1,5 +1,5 @@
 // C ABI of the s3a library: handle, workspace, argument checks, launch
-// sequences (plain per-pair and batched), graph capture, autotuning.
+// sequences (plain per-pair and batched), autotuning.
 #include <math.h>
 #include <string.h>
 
@@ -16,22 +16,6 @@
 using namespace s3a;
 
 namespace {
-
-struct GraphKey {
-  int dtype, n_pairs, K, wg, items, occupancy, window, persistent;
-  int64_t n_points;
-  uint32_t flags;
-  float tau;
-  double delta;
-  const void* ptrs[12];
-  bool operator==(const GraphKey& o) const { return memcmp(this, &o, sizeof(GraphKey)) == 0; }
-};
-
-struct GraphEntry {
-  GraphKey key;
-  hipGraphExec_t exec;
-  uint64_t used;
-};
 
 struct TuneEntry {
   int dtype;
@@ -50,9 +34,6 @@ struct s3a_handle {
   int64_t cap_tiles = 0;
   int cap_pairs = 0;
   Work w{};
-  hipStream_t capture_stream = nullptr;
-  std::vector<GraphEntry> graphs;
-  uint64_t clock = 0;
   bool forced[2] = {false, false};
   LaunchCfg forced_cfg[2];
   std::vector<TuneEntry> tuned;
@@ -144,11 +125,6 @@ struct DeviceGuard {
   }
 };
 
-void clear_graphs(s3a_handle* h) {
-  for (auto& g : h->graphs) (void)hipGraphExecDestroy(g.exec);
-  h->graphs.clear();
-}
-
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 int ensure_workspace(s3a_handle* h, int n_pairs, int64_t tiles) {
@@ -157,16 +133,15 @@ int ensure_workspace(s3a_handle* h, int n_pairs, int64_t tiles) {
   const int64_t nt = std::max<int64_t>(tiles, std::max<int64_t>(h->cap_tiles, 1024));
   size_t off = 0;
   const size_t o_tiles = off; off = align_up(off + sizeof(TileDesc) * nt);
-  const size_t o_part = off;  off = align_up(off + sizeof(double) * NSTAT * nt);
+  const size_t o_part = off;  off = align_up(off + sizeof(double) * NSTAT * 2 * nt);
   const size_t o_sched = off; off = align_up(off + sizeof(PairSched) * np);
   const size_t o_par = off;   off = align_up(off + sizeof(PointParams) * np);
-  const size_t o_state = off; off = align_up(off + sizeof(PairState) * np);
+  const size_t o_state = off; off = align_up(off + sizeof(PairState) * 2 * np);
   const size_t o_cnt = off;   off = align_up(off + sizeof(uint32_t) * (np + 64));
   const size_t o_flag = off;  off = align_up(off + sizeof(uint32_t) * (np + 64));
   const size_t o_tot = off;   off = align_up(off + sizeof(int32_t) * 64);
   const size_t o_desc = off;  off = align_up(off + sizeof(CallDesc));
   const size_t o_dpair = off; off = align_up(off + sizeof(DepthPair) * np);
-  clear_graphs(h);
   if (h->ws) {
     (void)hipDeviceSynchronize();
     (void)hipFree(h->ws);
@@ -191,6 +166,8 @@ int ensure_workspace(s3a_handle* h, int n_pairs, int64_t tiles) {
   h->w.flags = reinterpret_cast<uint32_t*>(b + o_flag);
   h->w.total_tiles = reinterpret_cast<int32_t*>(b + o_tot);
   h->w.scan_tmp = nullptr;
+  h->w.tiles_cap = nt;
+  h->w.pairs_cap = np;
   h->desc = reinterpret_cast<CallDesc*>(b + o_desc);
   h->w.dpairs = reinterpret_cast<DepthPair*>(b + o_dpair);
   h->cap_pairs = np;
@@ -253,6 +230,15 @@ LaunchCfg pick_cfg(s3a_handle* h, int dtype, int64_t n_points) {
   return default_cfg(dtype);
 }
 
+// A shape was forced or tuned for calls of this kind and size class.
+bool has_cfg(s3a_handle* h, int dtype, int64_t n_points) {
+  if (h->forced[dtype & 1]) return true;
+  const int sc = size_class(n_points);
+  for (auto& t : h->tuned)
+    if (t.dtype == dtype && t.size_class == sc) return true;
+  return false;
+}
+
 bool valid_cfg(const LaunchCfg& c) {
   return (c.wg == 256 || c.wg == 512) && (c.items == 2 || c.items == 4 || c.items == 8 || (c.items == 16 && c.wg == 256)) &&
          c.occupancy >= 0 &&
@@ -282,8 +268,8 @@ CallDesc make_call(const s3a_align_desc* d) {
   return c;
 }
 
-// The CallDesc travels to the device inside the workspace: copied on the
-// stream just before the kernels that read it.
+// The CallDesc lies in the workspace: the schedule launch, which takes it as an
+// argument, stores it there for the kernels that follow.
 CallDesc* desc_slot(s3a_handle* h) { return h->desc; }
 
 // Occupancy 0: one workgroup per tile (the hardware balances the tail);
@@ -294,16 +280,11 @@ int grid_for(s3a_handle* h, const LaunchCfg& lc, int64_t tiles) {
   return (int)std::max<int64_t>(g, 1);
 }
 
-// Multi-launch batched sequence: schedule, then per pass one streaming launch
+// Multi-launch batched sequence after the schedule: per pass one streaming launch
 // over every tile of every pair and one finalize launch.
-hipError_t enqueue_batched_multi(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
-                                 hipStream_t st) {
-  hipError_t e = launch_sched(sh, dcd, h->w, st);
-  if (e != hipSuccess) return e;
-  if (dtype == DT_DEPTH_F32 || dtype == DT_DEPTH_BF16) {
-    e = launch_depth_prep(sh, dcd, h->w, st);
-    if (e != hipSuccess) return e;
-  }
+hipError_t enqueue_batched(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
+                           hipStream_t st) {
+  hipError_t e = hipSuccess;
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
   const int grid = grid_for(h, lc, mt);
   const int npass = 1 + sh.K + ((sh.flags & S3A_FLAG_FINAL_COST) ? 1 : 0);
@@ -314,19 +295,42 @@ hipError_t enqueue_batched_multi(s3a_handle* h, int dtype, const LaunchCfg& lc, 
       e = launch_pass(dtype, mode, lc, sh, dcd, h->w, 0, -1, grid, st);
     }
     if (e != hipSuccess) return e;
-    const int kind = pass == 0 ? 0 : (pass <= sh.K ? 1 : 2);
-    e = launch_finalize(kind, sh, dcd, h->w, pass, 0, sh.n_pairs, st);
+    e = launch_finalize(sh, dcd, h->w, pass, 0, sh.n_pairs, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-hipError_t enqueue_batched(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
-                           bool persistent, hipStream_t st) {
-  if (!persistent) return enqueue_batched_multi(h, dtype, lc, sh, dcd, st);
-  hipError_t e = launch_sched(sh, dcd, h->w, st);
-  if (e != hipSuccess) return e;
-  e = launch_fill_zero(h->w.counters, (int64_t)sh.n_pairs + 64, st);
+// Whether an untuned call's passes solve the pass before themselves (k_pass_solve)
+// instead of a finalize launch between passes. It saves that launch, about 2.5 us of
+// a pass, and repeats the solve and the gather of the pair's partials in every
+// workgroup. Measured, finalize launches against solving passes, 10 steps: one pair
+// of 3,072 points 113 -> 96 us; 10 pairs of 200,000 FP32 193 -> 165, 20 pairs (1,000
+// tiles) 287 -> 259, 40 pairs 477 -> 469; BF16, 16 pairs 218 -> 193, 32 pairs (1,600
+// tiles) 289 -> 294; depth frames of 203,056 pixels, 20 pairs (260 tiles, the chip's
+// workgroups at once) 365 -> 343, 40 pairs 430 -> 504. A pair of many tiles pays for
+// the gather: one pair of 2 M points (490 tiles) 208 -> 186, of 4 M 329 -> 350.
+bool passes_solve(s3a_handle* h, int dtype, int64_t n_points, int n_pairs, int64_t tiles) {
+  if (has_cfg(h, dtype, n_points)) return false;
+  const bool depth = dtype == DT_DEPTH_F32 || dtype == DT_DEPTH_BF16;
+  return tiles <= (depth ? 1 : 4) * (int64_t)h->n_cu && tiles <= 512 * (int64_t)n_pairs;
+}
+
+hipError_t enqueue_solving(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
+                           int grid, hipStream_t st) {
+  const int last = sh.K + ((sh.flags & S3A_FLAG_FINAL_COST) ? 1 : 0);
+  for (int pass = 0; pass <= last; ++pass) {
+    TimedLaunch tl(h, st);
+    const hipError_t e = pass == 0 ? launch_pass(dtype, MODE_MOMENTS, lc, sh, dcd, h->w, 0, -1, grid, st)
+                                   : launch_pass_solve(dtype, sh, dcd, h->w, pass, grid, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_solve_last(sh, dcd, h->w, last, st);
+}
+
+hipError_t enqueue_persistent(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
+                              hipStream_t st) {
+  hipError_t e = launch_fill_zero(h->w.counters, (int64_t)sh.n_pairs + 64, st);
   if (e != hipSuccess) return e;
   e = launch_fill_zero(h->w.flags, (int64_t)sh.n_pairs, st);
   if (e != hipSuccess) return e;
@@ -373,14 +377,8 @@ int s3a_create(s3a_handle** out, int device) {
     return S3A_EHIP;
   }
   h->n_cu = prop.multiProcessorCount;
-  e = hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking);
-  if (e != hipSuccess) {
-    delete h;
-    return S3A_EHIP;
-  }
   e = hipEventCreateWithFlags(&h->order_ev, hipEventDisableTiming);
   if (e != hipSuccess) {
-    (void)hipStreamDestroy(h->capture_stream);
     delete h;
     return S3A_EHIP;
   }
@@ -392,14 +390,12 @@ int s3a_destroy(s3a_handle* h) {
   if (!h) return S3A_EINVAL;
   DeviceGuard g(h->device);
   (void)hipDeviceSynchronize();
-  clear_graphs(h);
   if (h->ws) (void)hipFree(h->ws);
   if (h->flags_dev) (void)hipFree(h->flags_dev);
   if (h->hpart) (void)hipFree(h->hpart);
   pgo_free(h->pgo);
   for (auto& ev : h->ev_used) { (void)hipEventDestroy(ev.first); (void)hipEventDestroy(ev.second); }
   for (auto& ev : h->ev_free) { (void)hipEventDestroy(ev.first); (void)hipEventDestroy(ev.second); }
-  if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
   if (h->order_ev) (void)hipEventDestroy(h->order_ev);
   delete h;
   return S3A_OK;
@@ -433,9 +429,7 @@ int align_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_pair* dept
 
   if (d->flags & S3A_FLAG_PLAIN) {
     // one pair at a time: read the schedule back, then 1 + K (+1) passes per pair
-    S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-    S3A_TRY(launch_sched(sh, dcd, h->w, st));
-    if (depth) S3A_TRY(launch_depth_prep(sh, dcd, h->w, st));
+    S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
     std::vector<PairSched> sched(d->n_pairs);
     S3A_TRY(hipMemcpyAsync(sched.data(), h->w.sched, sizeof(PairSched) * d->n_pairs, hipMemcpyDeviceToHost, st));
     S3A_TRY(hipStreamSynchronize(st));
@@ -448,67 +442,19 @@ int align_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_pair* dept
           TimedLaunch tl(h, st);
           S3A_TRY(launch_pass(d->dtype, mode, lc, sh, dcd, h->w, s.tile0, s.tile0 + s.ntiles, s.ntiles, st));
         }
-        const int kind = pass == 0 ? 0 : (pass <= sh.K ? 1 : 2);
-        S3A_TRY(launch_finalize(kind, sh, dcd, h->w, pass, k, 1, st));
+        S3A_TRY(launch_finalize(sh, dcd, h->w, pass, k, 1, st));
       }
     }
     return S3A_OK;
   }
 
-  const bool persistent = (d->flags & S3A_FLAG_PERSISTENT) != 0;
-  if ((d->flags & S3A_FLAG_NO_GRAPH) || h->timing) {
-    S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-    S3A_TRY(enqueue_batched(h, d->dtype, lc, sh, dcd, persistent, st));
-    return S3A_OK;
-  }
-
-  // graph path: the descriptor copy stays outside the graph; the graph is keyed
-  // on the shape and launch configuration (pointers reach the kernels through
-  // the descriptor, so a graph serves every call of that shape)
-  GraphKey key;
-  memset(&key, 0, sizeof(key));
-  key.dtype = d->dtype;
-  key.n_pairs = d->n_pairs;
-  key.K = sh.K;
-  key.wg = lc.wg;
-  key.items = lc.items;
-  key.occupancy = lc.occupancy;
-  key.window = lc.window;
-  key.persistent = persistent;
-  key.n_points = d->n_points;
-  key.flags = d->flags;
-  key.tau = d->conf_threshold;
-  key.delta = d->huber_delta;
-  key.ptrs[0] = h->ws;
-  hipGraphExec_t exec = nullptr;
-  for (auto& ge : h->graphs)
-    if (ge.key == key) {
-      exec = ge.exec;
-      ge.used = ++h->clock;
-    }
-  if (!exec) {
-    hipGraph_t graph = nullptr;
-    S3A_TRY(hipStreamBeginCapture(h->capture_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = enqueue_batched(h, d->dtype, lc, sh, dcd, persistent, h->capture_stream);
-    hipError_t e2 = hipStreamEndCapture(h->capture_stream, &graph);
-    if (e != hipSuccess) {
-      if (graph) (void)hipGraphDestroy(graph);
-      return hip_fail(h, e);
-    }
-    if (e2 != hipSuccess) return hip_fail(h, e2);
-    e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) return hip_fail(h, e);
-    if (h->graphs.size() >= 16) {
-      auto it = std::min_element(h->graphs.begin(), h->graphs.end(),
-                                 [](const GraphEntry& a, const GraphEntry& b) { return a.used < b.used; });
-      (void)hipGraphExecDestroy(it->exec);
-      h->graphs.erase(it);
-    }
-    h->graphs.push_back(GraphEntry{key, exec, ++h->clock});
-  }
-  S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-  S3A_TRY(hipGraphLaunch(exec, st));
+  S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
+  if (d->flags & S3A_FLAG_PERSISTENT)
+    S3A_TRY(enqueue_persistent(h, d->dtype, lc, sh, dcd, st));
+  else if (passes_solve(h, d->dtype, d->n_points, d->n_pairs, mt))
+    S3A_TRY(enqueue_solving(h, d->dtype, lc, sh, dcd, (int)mt, st));
+  else
+    S3A_TRY(enqueue_batched(h, d->dtype, lc, sh, dcd, st));
   return S3A_OK;
 }
 
@@ -565,11 +511,6 @@ int noalloc_scratch(unsigned char** out) {
   return S3A_OK;
 }
 
-// The call's descriptor reaches the device as a kernel argument (no host copy).
-__global__ void k_store_desc(CallDesc c, CallDesc* dst) {
-  if (threadIdx.x == 0) *dst = c;
-}
-
 // Fixed launch shapes: 8192-element tiles, one workgroup per tile.
 LaunchCfg noalloc_cfg(int dtype) {
   LaunchCfg c;
@@ -615,20 +556,18 @@ int s3a_align_pairs_noalloc(const s3a_align_desc* d, const s3a_sim3* init, s3a_s
   c.info = info;
   CallDesc* dcd = reinterpret_cast<CallDesc*>(base + NA_O_DESC);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_store_desc, dim3(1), dim3(64), 0, st, c, dcd);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(nullptr, e);
   // every scratch word a kernel reads is written earlier in the same call:
-  // the schedule and tile table by k_sched/k_sched_fill, each tile's partials
-  // by its pass, each pair's state and parameters by the moments finalize
-  e = launch_sched(sh, dcd, w, st);
+  // the descriptor, schedule and tile table by the schedule launch (which takes the
+  // descriptor as an argument: no host copy), each tile's partials by its pass, each
+  // pair's state and parameters by the moments finalize
+  hipError_t e = launch_sched(sh, c, dcd, w, st);
   if (e != hipSuccess) return hip_fail(nullptr, e);
   const int grid = (int)std::max<int64_t>(mt, 1);
   const int npass = 1 + sh.K + ((sh.flags & S3A_FLAG_FINAL_COST) ? 1 : 0);
   for (int pass = 0; pass < npass; ++pass) {
     e = launch_pass(d->dtype, pass_mode(pass, sh.K), lc, sh, dcd, w, 0, -1, grid, st);
     if (e != hipSuccess) return hip_fail(nullptr, e);
-    e = launch_finalize(pass == 0 ? 0 : (pass <= sh.K ? 1 : 2), sh, dcd, w, pass, 0, sh.n_pairs, st);
+    e = launch_finalize(sh, dcd, w, pass, 0, sh.n_pairs, st);
     if (e != hipSuccess) return hip_fail(nullptr, e);
   }
   return S3A_OK;
@@ -708,8 +647,7 @@ int s3a_align_cost(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, co
   c.L_out = L_out;
   c.C_out = C_out;
   CallDesc* dcd = desc_slot(h);
-  S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-  S3A_TRY(launch_sched(sh, dcd, h->w, st));
+  S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
   S3A_TRY(launch_prep(sh, dcd, h->w, 0, st));
   {
     TimedLaunch tl(h, st);
@@ -748,8 +686,7 @@ int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_s
   for (int j = 0; j < 7; ++j) c.grad[j] = gr[j];
   c.gxi = gxi;
   CallDesc* dcd = desc_slot(h);
-  S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-  S3A_TRY(launch_sched(sh, dcd, h->w, st));
+  S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
   S3A_TRY(launch_prep(sh, dcd, h->w, 1, st));
   {
     TimedLaunch tl(h, st);
@@ -796,8 +733,7 @@ int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* d, co
   c.xi = nullptr;
   for (int j = 0; j < 7; ++j) c.grad[j] = gr[j];
   CallDesc* dcd = desc_slot(h);
-  S3A_TRY(hipMemcpyAsync(dcd, &c, sizeof(c), hipMemcpyHostToDevice, st));
-  S3A_TRY(launch_sched(sh, dcd, h->w, st));
+  S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
   S3A_TRY(launch_prep(sh, dcd, h->w, 0, st));
   TimedLaunch tl(h, st);
   S3A_TRY(launch_implicit(d->dtype, lc, sh, dcd, h->w, h->hpart, gS, iflags, v_out, status_out, grid_for(h, lc, mt), mt,
@@ -878,13 +814,40 @@ static int autotune_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_
   const bool was_forced = h->forced[plane];
   const LaunchCfg was_cfg = h->forced_cfg[plane];
   LaunchCfg bestc = default_cfg(d->dtype);
-  float best_ms = 1e30f;
   const int wgs[2] = {256, 512};
   const int its[4] = {2, 4, 8, 16};
   const int occs[4] = {0, 2, 4, 8};
   const bool persistent = (d->flags & S3A_FLAG_PERSISTENT) && !(d->flags & S3A_FLAG_PLAIN);
   s3a_align_desc dd = *d;
   dd.flags &= ~S3A_FLAG_PLAIN;
+  // the call's time in the shape in force (1e30 when it fails)
+  auto timed = [&]() -> float {
+    float ms = 1e30f;
+    for (int rep = 0; rep < 4; ++rep) {
+      if (align_run(h, &dd, depth, nullptr, S, nullptr, stream) != S3A_OK) return 1e30f;
+      if (rep == 0) {  // warm-up
+        if (hipStreamSynchronize(st) != hipSuccess) return 1e30f;
+        continue;
+      }
+      (void)hipEventRecord(e0, st);
+      if (align_run(h, &dd, depth, nullptr, S, nullptr, stream) != S3A_OK) return 1e30f;
+      (void)hipEventRecord(e1, st);
+      if (hipEventSynchronize(e1) != hipSuccess) return 1e30f;
+      float t = 0.0f;
+      (void)hipEventElapsedTime(&t, e0, e1);
+      ms = std::min(ms, t);
+    }
+    return ms;
+  };
+  // an untuned call may solve in its passes, which no tuned shape does: it is kept
+  // unless a shape is faster
+  const int sc = size_class(d->n_points);
+  h->tuned.erase(std::remove_if(h->tuned.begin(), h->tuned.end(),
+                                [&](const TuneEntry& t) { return t.dtype == d->dtype && t.size_class == sc; }),
+                 h->tuned.end());
+  h->forced[plane] = false;
+  float best_ms = timed();
+  bool shaped = false;
   for (int wg : wgs)
     for (int it : its)
       for (int oc : occs) {
@@ -897,25 +860,11 @@ static int autotune_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_
         c.window = 0;
         h->forced[plane] = true;
         h->forced_cfg[plane] = c;
-        float ms = 1e30f;
-        bool ok = true;
-        for (int rep = 0; rep < 4 && ok; ++rep) {
-          if (align_run(h, &dd, depth, nullptr, S, nullptr, stream) != S3A_OK) ok = false;
-          if (rep == 0) {  // warm-up (and graph capture)
-            if (hipStreamSynchronize(st) != hipSuccess) ok = false;
-            continue;
-          }
-          (void)hipEventRecord(e0, st);
-          if (align_run(h, &dd, depth, nullptr, S, nullptr, stream) != S3A_OK) ok = false;
-          (void)hipEventRecord(e1, st);
-          if (hipEventSynchronize(e1) != hipSuccess) ok = false;
-          float t = 0.0f;
-          (void)hipEventElapsedTime(&t, e0, e1);
-          ms = std::min(ms, t);
-        }
-        if (ok && ms < best_ms) {
+        const float ms = timed();
+        if (ms < best_ms) {
           best_ms = ms;
           bestc = c;
+          shaped = true;
         }
       }
   h->forced[plane] = was_forced;
@@ -923,14 +872,7 @@ static int autotune_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   (void)hipFree(S);
-  const int sc = size_class(d->n_points);
-  bool found = false;
-  for (auto& t : h->tuned)
-    if (t.dtype == d->dtype && t.size_class == sc) {
-      t.cfg = bestc;
-      found = true;
-    }
-  if (!found) h->tuned.push_back(TuneEntry{d->dtype, sc, bestc});
+  if (shaped) h->tuned.push_back(TuneEntry{d->dtype, sc, bestc});
   if (best) {
     best->wg = bestc.wg;
     best->items = bestc.items;

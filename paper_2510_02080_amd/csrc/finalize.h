@@ -131,25 +131,26 @@ __device__ inline bool state_from_moments(const Shape& sh, const s3a_sim3* init,
 // 17 statistics, Cholesky solve, map the step back, S <- Exp(xi) S. The
 // reported H, g are those of the uncentred Jacobian, rebuilt from the same
 // statistics shifted back by the centre c (y = y_c + c). Returns whether passes
-// follow. The state is read at the start in one batch (its latency is paid once).
+// follow. The state lies in LDS, so it is read where it is used: held in registers
+// from the start it would cost a wavefront of occupancy in k_pass_solve.
 __device__ inline bool state_from_gn(const Shape& sh, int pass, const double* s, PairState* st) {
-  const double c[3] = {st->cq[0], st->cq[1], st->cq[2]};
-  const double C = st->C;
-  const Sim3d S = st->S;
-  st->cost_lin = s[17] / C;  // the cost and inlier count at the linearisation point
-  st->inl_lin = (int64_t)s[18];
   double Hp[28], g[7], x[7];
   assemble_gn_packed(s, Hp, g);
   for (int i = 0; i < 7; ++i) g[i] = -g[i];
   int status = S3A_PAIR_OK;
-  if (cholesky_solve_packed<7>(Hp, g, x)) {
+  const bool spd = cholesky_solve_packed<7>(Hp, g, x);
+  __builtin_amdgcn_sched_barrier(0);
+  const double c[3] = {st->cq[0], st->cq[1], st->cq[2]};
+  if (spd) {
     // xi = Ad(translation c) xi': rho = rho' + c x omega - sigma c
     double xi[7];
     xi[0] = x[0] + (c[1] * x[5] - c[2] * x[4]) - x[6] * c[0];
     xi[1] = x[1] + (c[2] * x[3] - c[0] * x[5]) - x[6] * c[1];
     xi[2] = x[2] + (c[0] * x[4] - c[1] * x[3]) - x[6] * c[2];
     for (int i = 3; i < 7; ++i) xi[i] = x[i];
-    const Sim3d Snew = sim3_compose(sim3_exp(xi), S);
+    const Sim3d E = sim3_exp(xi);
+    __builtin_amdgcn_sched_barrier(0);
+    const Sim3d Snew = sim3_compose(E, st->S);
     if (!sim3_finite(Snew)) {
       status = S3A_PAIR_NONFINITE;
     } else {
@@ -157,7 +158,11 @@ __device__ inline bool state_from_gn(const Shape& sh, int pass, const double* s,
       st->iters = pass;
     }
     if (status == S3A_PAIR_OK && pass == sh.K) {
-      // Reported with the last step only: uncentred statistics, y = y_c + c
+      // Reported with the last step only: the cost and inlier count at the
+      // linearisation point, and uncentred statistics, y = y_c + c
+      const double C = st->C;
+      st->cost_lin = s[17] / C;
+      st->inl_lin = (int64_t)s[18];
       double u[17];
       const double A0 = s[0], a[3] = {s[1], s[2], s[3]}, br[3] = {s[10], s[11], s[12]};
       u[0] = A0;
@@ -188,28 +193,86 @@ __device__ inline bool state_from_gn(const Shape& sh, int pass, const double* s,
   return status == S3A_PAIR_OK && (pass < sh.K || (sh.flags & S3A_FLAG_FINAL_COST) != 0);
 }
 
-// The same on the call's per-pair state and parameters in device memory.
-__device__ inline void finalize_moments(const Shape& sh, const CallDesc* cd, Work& w, int k, const PairSched& sc,
-                                        const double* s) {
-  PairState* st = w.state + k;
-  const bool more = state_from_moments(sh, cd->init ? cd->init + k : nullptr, sc.bad != 0, s, st);
-  if (!more) write_outputs(cd, k, *st, __builtin_nan(""), 0);
-  publish(w.params + k, st->S, st->cq, more ? 1 : 0, st->nnf > 0 ? 1 : 0);
+// ---------------------------------------------------------------- the solve after a pass
+
+// What a workgroup keeps in LDS while it solves a pair.
+constexpr int STATE_WORDS = sizeof(PairState) / 8;
+static_assert(sizeof(PairState) % 8 == 0 && STATE_WORDS <= 64, "one word a lane");
+constexpr int SOLVE_GROUPS = 12;  // groups of NSTAT lanes that gather partials, three a wavefront
+struct SolveLds {
+  double part[SOLVE_GROUPS][NSTAT];
+  double sums[NSTAT];
+  PairState st;
+  int32_t more;
+};
+
+// The gather of a pair's tile partials: group g adds the tiles g, g + 12, ... in
+// order, a statistic per lane (one coalesced load a tile, eight in flight), into
+// part[g]; the sums are then the twelve groups' in order. Wavefront wv of nw takes
+// every nw-th trio of groups, so the result does not depend on nw.
+__device__ inline void gather_groups(const double* p, int ntiles, int wv, int nw, double (*part)[NSTAT]) {
+  const int lane = (int)threadIdx.x & 63, g = lane / NSTAT, j = lane % NSTAT;
+  for (int r = wv; r < SOLVE_GROUPS / 3; r += nw) {
+    if (g >= 3) continue;
+    double s = 0.0;
+#pragma unroll 1
+    for (int q = 3 * r + g; q < ntiles; q += 8 * SOLVE_GROUPS) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = q + u * SOLVE_GROUPS < ntiles ? p[(size_t)(q + u * SOLVE_GROUPS) * NSTAT + j] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    part[3 * r + g][j] = s;
+  }
 }
 
-__device__ inline void finalize_gn(const Shape& sh, const CallDesc* cd, Work& w, int k, int pass, const double* s) {
-  PairState* st = w.state + k;
-  if (st->status != S3A_PAIR_OK || !w.params[k].active) return;
-  const bool more = state_from_gn(sh, pass, s, st);
-  if (!more) write_outputs(cd, k, *st, __builtin_nan(""), 0);
-  publish(w.params + k, st->S, st->cq, more ? 1 : 0, st->nnf > 0 ? 1 : 0);
+// By the first wavefront, with every group in S.part and the pair's state in S.st:
+// the sums, then by one lane the solve after pass `done` (0: the closed form, then
+// the K steps, K + 1: the cost at the final iterate). The new state to S.st, whether
+// passes follow to S.more; where none does, and `write`, the outputs.
+enum SolveKind { SOLVE_MOMENTS, SOLVE_GN, SOLVE_ANY };
+template <SolveKind KIND>
+__device__ inline void solve_wave(const Shape& sh, const CallDesc* __restrict__ cd, int k, int done, bool bad, bool write,
+                                  SolveLds& S) {
+  const int lane = (int)threadIdx.x & 63;
+  if (lane < NSTAT) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < SOLVE_GROUPS; ++q) t += S.part[q][lane];
+    S.sums[lane] = t;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  if (lane == 0) {
+    bool more = false, ended = false;
+    double fcost = __builtin_nan("");
+    int64_t finl = 0;
+    if (KIND == SOLVE_MOMENTS || (KIND == SOLVE_ANY && done == 0)) {
+      more = state_from_moments(sh, cd->init ? cd->init + k : nullptr, bad, S.sums, &S.st);
+      ended = !more;
+    } else if (S.st.status == S3A_PAIR_OK) {
+      if (done <= sh.K) {
+        more = state_from_gn(sh, done, S.sums, &S.st);
+      } else {
+        fcost = S.sums[17] / S.st.C;
+        finl = (int64_t)S.sums[18];
+      }
+      ended = !more;
+    }  // else it failed in an earlier pass, whose solve wrote its outputs
+    if (ended && write) write_outputs(cd, k, S.st, fcost, finl);
+    S.more = more ? 1 : 0;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
-__device__ inline void finalize_final_cost(const CallDesc* cd, Work& w, int k, const double* s) {
-  const PairState* st = w.state + k;
-  if (st->status != S3A_PAIR_OK || !w.params[k].active) return;
-  write_outputs(cd, k, *st, s[17] / st->C, (int64_t)s[18]);
-  w.params[k].active = 0;
+// The state's words between device memory and LDS, one a lane.
+__device__ inline double state_word(const PairState* st) {
+  const int lane = (int)threadIdx.x & 63;
+  return lane < STATE_WORDS ? reinterpret_cast<const double*>(st)[lane] : 0.0;
+}
+__device__ inline void set_state_word(PairState* st, double v) {
+  const int lane = (int)threadIdx.x & 63;
+  if (lane < STATE_WORDS) reinterpret_cast<double*>(st)[lane] = v;
 }
 
 }  // namespace s3a

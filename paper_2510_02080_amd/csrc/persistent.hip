@@ -57,6 +57,10 @@ __global__ void k_init_outputs(Shape sh, const CallDesc* __restrict__ cd) {
   }
 }
 
+// Every store of this wavefront acknowledged (the state's words are stored by its
+// lanes, the flag that releases them by one).
+__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ inline uint32_t ld_acquire(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -64,6 +68,7 @@ __device__ inline uint32_t ld_acquire(const uint32_t* p) {
 template <int DT, int WG, int ITEMS>
 __global__ __launch_bounds__(WG, 2) void k_persistent(Shape sh, const CallDesc* __restrict__ cd, Work w) {
   __shared__ double red[WG / 64][NSTAT];
+  __shared__ SolveLds S;
   __shared__ unsigned long long s_ticket;
   __shared__ int s_flag;
   const int npass = 1 + sh.K + ((sh.flags & S3A_FLAG_FINAL_COST) ? 1 : 0);
@@ -119,12 +124,14 @@ __global__ __launch_bounds__(WG, 2) void k_persistent(Shape sh, const CallDesc* 
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       if (threadIdx.x < 64) {
         const PairSched sc = w.sched[j];
-        double s[NSTAT];
-        pair_sums(w, sc, NSTAT, s);
+        gather_groups(w.partials + (int64_t)sc.tile0 * NSTAT, sc.ntiles, 0, 1, S.part);
+        if (pass > 0) set_state_word(&S.st, state_word(w.state + j));
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        solve_wave<SOLVE_ANY>(sh, cd, j, pass, sc.bad != 0, true, S);
+        set_state_word(w.state + j, state_word(&S.st));
+        stores_done();
         if (threadIdx.x == 0) {
-          if (pass == 0) finalize_moments(sh, cd, w, j, sc, s);
-          else if (pass <= sh.K) finalize_gn(sh, cd, w, j, pass, s);
-          else finalize_final_cost(cd, w, j, s);
+          publish(w.params + j, S.st.S, S.st.cq, S.more, S.st.nnf > 0 ? 1 : 0);
           arrive[j] = 0u;
           __threadfence();
           __hip_atomic_store(w.flags + j, (uint32_t)(pass + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);

@@ -65,6 +65,8 @@ struct TileDesc {
   int64_t end;    // one past the last element of this tile
   int64_t lo;     // first element of the pair (elements in [begin, lo) are masked)
   int32_t pair;
+  int32_t tile0;  // the pair's first tile and tile count (PairSched's, beside the tile
+  int32_t ntiles; // so that a pass needs one load before it can issue the others)
   int32_t pad;
 };
 
@@ -143,8 +145,10 @@ struct Work {
   TileDesc* tiles;
   PairSched* sched;
   PointParams* params;
-  PairState* state;
-  double* partials;    // [max_tiles][NSTAT]
+  PairState* state;    // [2][pairs]
+  double* partials;    // [2][tiles][NSTAT] (the second buffer: passes that solve, see k_pass_solve)
+  int64_t tiles_cap;   // tiles of one buffer
+  int32_t pairs_cap;   // pairs of one buffer of state
   int32_t* total_tiles;
   uint32_t* counters;  // [n_pairs] arrivals, then 4 scheduling words
   uint32_t* flags;     // [n_pairs] per-pair published pass (persistent launch)
