@@ -53,18 +53,25 @@ __device__ inline bool depth_prep(const s3a_depth_pair& src, int64_t n, DepthPai
   return ok;
 }
 
-// Tile j of a pair's range [a, b).
-__device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, int ntiles, int j, int64_t T) {
+// Tile j of a pair's range [a, b); depth: the pair's frames, or null. Frames narrower
+// than a vector count as spanned (their pixels go one at a time: see DepthWalk).
+__device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, int ntiles, int j, int64_t T,
+                                     const s3a_depth_pair* depth) {
   const int64_t b0 = a & ~(TILE_ALIGN - 1);
   TileDesc t;
   t.pair = pair;
   t.tile0 = tile0;
   t.ntiles = ntiles;
-  t.pad = 0;
+  t.frame = -1;
   if (b > a) {
     t.begin = b0 + (int64_t)j * T;
     t.end = t.begin + T < b ? t.begin + T : b;
     t.lo = a;
+    if (depth && depth->width >= 8 && depth->frame_pixels >= depth->width) {
+      const int64_t first = t.begin > a ? t.begin : a;
+      const int f0 = (int)((first - a) / depth->frame_pixels), f1 = (int)((t.end - 1 - a) / depth->frame_pixels);
+      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first) t.frame = f0;
+    }
   } else {
     t.begin = t.end = t.lo = a;
   }
@@ -140,7 +147,7 @@ __global__ __launch_bounds__(SCHED_WG) void k_sched_tiles(Shape sh, CallDesc c, 
       else hi = mid - 1;
     }
     const int64_t a = any_bad ? 0 : c.offsets[lo], b = any_bad ? 0 : c.offsets[lo + 1];
-    w.tiles[t] = make_tile(a, b, lo, tile0[lo], tile0[lo + 1] - tile0[lo], t - tile0[lo], T);
+    w.tiles[t] = make_tile(a, b, lo, tile0[lo], tile0[lo + 1] - tile0[lo], t - tile0[lo], T, c.depth ? c.depth + lo : nullptr);
   }
 }
 
@@ -195,11 +202,11 @@ __global__ __launch_bounds__(1024) void k_sched(Shape sh, CallDesc c, CallDesc* 
   }
 }
 
-__global__ void k_sched_fill(Shape sh, Work w) {
+__global__ void k_sched_fill(Shape sh, const s3a_depth_pair* depth, Work w) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= sh.n_pairs) return;
   const PairSched s = w.sched[k];
-  for (int j = 0; j < s.ntiles; ++j) w.tiles[s.tile0 + j] = make_tile(s.a, s.b, k, s.tile0, s.ntiles, j, sh.tile_elems);
+  for (int j = 0; j < s.ntiles; ++j) w.tiles[s.tile0 + j] = make_tile(s.a, s.b, k, s.tile0, s.ntiles, j, sh.tile_elems, depth ? depth + k : nullptr);
 }
 
 __global__ void k_depth_prep(Shape sh, const CallDesc* __restrict__ cd, Work w) {
@@ -211,7 +218,9 @@ __global__ void k_depth_prep(Shape sh, const CallDesc* __restrict__ cd, Work w) 
 
 // ------------------------------------------------------------------ point passes
 
-template <int DT, int MODE, int WG, int ITEMS>
+// ONE: a workgroup per tile, no loop over tiles (what the loop keeps in registers
+// costs a wavefront of occupancy on depth input).
+template <int DT, int MODE, int WG, int ITEMS, bool ONE>
 __global__ __launch_bounds__(WG) void k_pass(Shape sh, const CallDesc* __restrict__ cd, Work w,
                                               int32_t tile_lo, int32_t tile_hi) {
   __shared__ double red[WG / 64][NSTAT];
@@ -221,9 +230,12 @@ __global__ __launch_bounds__(WG) void k_pass(Shape sh, const CallDesc* __restric
   for (int j = 0; j < 7; ++j) pl[j] = cd->planes[j];
   for (int t = tile_lo + (int)blockIdx.x; t < total; t += (int)gridDim.x) {
     const TileDesc td = load_tile(w.tiles + t);
+    typename TileRaw<DT>::type first;
+    if constexpr (ONE) tile_begin<DT, WG>(sh, pl, td, first);
     const PointParams P = load_params(w.params + td.pair);
     const SrcCtx<DT> src = make_src<DT>(pl, w, td);
-    tile_body<DT, MODE, WG, ITEMS>(sh, src, td, P, red, w.partials + (int64_t)t * NSTAT);
+    tile_body<DT, MODE, WG, ITEMS, ONE>(sh, src, td, P, first, red, w.partials + (int64_t)t * NSTAT);
+    if constexpr (ONE) return;
   }
 }
 
@@ -271,9 +283,9 @@ __global__ __launch_bounds__(WG) void k_pass_solve(Shape sh, const CallDesc* __r
   const void* pl[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) pl[j] = cd->planes[j];
-  const SrcCtx<DT> src = make_src<DT>(pl, w, td);
   typename TileRaw<DT>::type first;
-  tile_begin<DT, WG>(sh, src, td, first);
+  tile_begin<DT, WG>(sh, pl, td, first);
+  const SrcCtx<DT> src = make_src<DT>(pl, w, td);
   if (!solve_pass<FIRST ? SOLVE_MOMENTS : SOLVE_GN>(sh, cd, w, td.pair, td.tile0, td.ntiles, pass - 1, t == td.tile0, S)) return;
   PointParams P;
 #pragma unroll
@@ -358,8 +370,15 @@ static hipError_t launch_pass_t(const LaunchCfg& lc, const Shape& sh, const Call
                                 int32_t tile_lo, int32_t tile_hi, int grid, hipStream_t st) {
 #define S3A_CASE(WGV, IT)                                                                                   \
   if (lc.wg == WGV && lc.items == IT) {                                                                     \
-    hipLaunchKernelGGL((k_pass<DT, MODE, WGV, IT>), dim3(grid), dim3(WGV), 0, st, sh, cd, w, tile_lo, tile_hi); \
+    hipLaunchKernelGGL((k_pass<DT, MODE, WGV, IT, false>), dim3(grid), dim3(WGV), 0, st, sh, cd, w, tile_lo, \
+                       tile_hi);                                                                            \
     return hipGetLastError();                                                                               \
+  }
+  if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
+    if (lc.wg == 256 && lc.items == 16 && lc.occupancy == 0) {  // the untuned depth shape
+      hipLaunchKernelGGL((k_pass<DT, MODE, 256, 16, true>), dim3(grid), dim3(256), 0, st, sh, cd, w, tile_lo, tile_hi);
+      return hipGetLastError();
+    }
   }
   S3A_CASE(256, 2) S3A_CASE(256, 4) S3A_CASE(256, 8) S3A_CASE(256, 16)
   S3A_CASE(512, 2) S3A_CASE(512, 4) S3A_CASE(512, 8)
@@ -406,7 +425,7 @@ hipError_t launch_sched(const Shape& sh, const CallDesc& c, CallDesc* cd, const 
   hipLaunchKernelGGL(k_sched, dim3(1), dim3(1024), 0, st, sh, c, cd, w);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sched_fill, dim3((sh.n_pairs + 255) / 256), dim3(256), 0, st, sh, w);
+  hipLaunchKernelGGL(k_sched_fill, dim3((sh.n_pairs + 255) / 256), dim3(256), 0, st, sh, c.depth, w);
   if ((e = hipGetLastError()) != hipSuccess || !c.depth) return e;
   hipLaunchKernelGGL(k_depth_prep, dim3((sh.n_pairs + 63) / 64), dim3(64), 0, st, sh, cd, w);
   return hipGetLastError();

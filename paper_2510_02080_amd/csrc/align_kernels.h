@@ -196,6 +196,28 @@ __device__ inline void pipelined_items(int end_rel, Fetch&& fetch, Body&& body) 
   pipelined_walk<WG, ITEMS, VEC, Raw, false>(end_rel, fetch, body, A);
 }
 
+// The walk of a full tile (every lane runs every item, every vector in bounds): the
+// next items' loads have no branch around them, so that the wait before an item
+// covers its own loads only (where a path may skip a load the compiler waits for
+// everything in flight, and a wavefront's next loads do not overlap its work). The
+// last item's loads are issued once more in place of those past the end.
+template <int WG, int ITEMS, int VEC, typename Raw, bool BEGUN, typename Fetch, typename Body>
+__device__ inline void full_walk(Fetch&& fetch, Body&& body, Raw& A) {
+  static_assert(ITEMS % 2 == 0, "two buffers in turn");
+  constexpr int STRIDE = WG * VEC;
+  const int first = (int)threadIdx.x * VEC;
+  Raw B;
+  if constexpr (!BEGUN) fetch(first, A);
+#pragma unroll 1
+  for (int it = 0; it < ITEMS; it += 2) {
+    const int r = first + it * STRIDE;
+    fetch(r + STRIDE, B);
+    body(A, r);
+    fetch(it + 2 < ITEMS ? r + 2 * STRIDE : r + STRIDE, A);
+    body(B, r + STRIDE);
+  }
+}
+
 // Gradients are written once and not read back by the library: streaming
 // (non-temporal) global stores.
 __device__ inline void store_grad_vec(float* base, int64_t g0, int64_t n, const float* v, int VEC, int64_t lo,
@@ -262,7 +284,7 @@ __device__ inline TileDesc load_tile(const TileDesc* p) {
   r.pair = uniform_i32(p->pair);
   r.tile0 = uniform_i32(p->tile0);
   r.ntiles = uniform_i32(p->ntiles);
-  r.pad = 0;
+  r.frame = uniform_i32(p->frame);
   return r;
 }
 
@@ -303,36 +325,8 @@ template <int DT>
 struct DepthPlanes {
   static constexpr bool BF = DT == DT_DEPTH_BF16;
   static constexpr int VEC = BF ? 8 : 4;
-  // d[0], d[1], d[2] = d_p, d_q, c of elements g0 .. g0 + VEC - 1 (0 past n)
-  __device__ static inline void load_raw(const SrcCtx<DT>& s, int64_t g0, int64_t n, float (&d)[3][VEC]) {
-    if (g0 + VEC <= n) {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        if constexpr (BF) {
-          const s3a_u4 x = __builtin_nontemporal_load((const S3A_GLOBAL s3a_u4*)(static_cast<const uint16_t*>(s.pl[j]) + g0));
-          d[j][0] = __uint_as_float(x.x << 16); d[j][1] = __uint_as_float(x.x & 0xffff0000u);
-          d[j][2] = __uint_as_float(x.y << 16); d[j][3] = __uint_as_float(x.y & 0xffff0000u);
-          d[j][4] = __uint_as_float(x.z << 16); d[j][5] = __uint_as_float(x.z & 0xffff0000u);
-          d[j][6] = __uint_as_float(x.w << 16); d[j][7] = __uint_as_float(x.w & 0xffff0000u);
-        } else {
-          const s3a_f4 x = __builtin_nontemporal_load((const S3A_GLOBAL s3a_f4*)(static_cast<const float*>(s.pl[j]) + g0));
-          d[j][0] = x.x; d[j][1] = x.y; d[j][2] = x.z; d[j][3] = x.w;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          if constexpr (BF)
-            d[j][e] = (g0 + e < n) ? __uint_as_float((uint32_t)static_cast<const uint16_t*>(s.pl[j])[g0 + e] << 16) : 0.0f;
-          else
-            d[j][e] = (g0 + e < n) ? static_cast<const float*>(s.pl[j])[g0 + e] : 0.0f;
-        }
-    }
-  }
-
-  // The same in two steps (raw 16-byte vectors first; see RawVec).
+  // Loads in two steps, as the stored planes' (see RawVec): d[0], d[1], d[2] = d_p, d_q,
+  // c of elements g0 .. g0 + VEC - 1 (0 past n)
   typedef s3a_u4 Raw[3];
   __device__ static inline void fetch(const SrcCtx<DT>& s, int64_t g0, int64_t n, Raw& r) {
     if (g0 + VEC <= n) {
@@ -357,6 +351,15 @@ struct DepthPlanes {
             r[j][i] = (g0 + i < n) ? static_cast<const uint32_t*>(s.pl[j])[g0 + i] : 0u;
           }
         }
+    }
+  }
+  // element rel of a tile from begin, every element in bounds (uniform bases and a
+  // 32-bit offset a lane)
+  __device__ static inline void fetch_full(const SrcCtx<DT>& s, int64_t begin, int rel, Raw& r) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const S3A_GLOBAL char* p = (const S3A_GLOBAL char*)s.pl[j] + begin * (BF ? 2 : 4);
+      r[j] = __builtin_nontemporal_load((const S3A_GLOBAL s3a_u4*)(p + (unsigned)rel * (BF ? 2u : 4u)));
     }
   }
   __device__ static inline void unpack(const Raw& r, float (&d)[3][VEC]) {
@@ -394,25 +397,31 @@ struct DepthPlanes {
     }
   }
 
-  __device__ static inline void load(const SrcCtx<DT>& s, int64_t g0, int64_t n, float (&v)[7][VEC]) {
-    float d[3][VEC];
-    load_raw(s, g0, n, d);
+  // The vector's elements one at a time, each unprojected with its own frame's
+  // cameras: point(x, rel) takes (p, q, c) and the element's offset from the vector's
+  // start. For the few tiles that span frames: kept small in registers (they set the
+  // occupancy of the kernels that hold it), not fast.
+  template <typename Point>
+  __device__ static inline void each(const SrcCtx<DT>& s, int64_t g0, int64_t n, Point&& point) {
+    Raw r;
+    fetch(s, g0, n, r);
     int f, row, col;
     position(s, g0, f, row, col);
-#pragma unroll
+#pragma unroll 1
     for (int e = 0; e < VEC; ++e) {
-      float x[3], y[3];
-      if (s.frame >= 0) {
-        unproject(s.cp, (float)col, (float)row, d[0][e], x);
-        unproject(s.cq, (float)col, (float)row, d[1][e], y);
-      } else {
-        const int fc = f < s.n_frames ? f : s.n_frames - 1;
-        unproject(s.dp->p[fc], (float)col, (float)row, d[0][e], x);
-        unproject(s.dp->q[fc], (float)col, (float)row, d[1][e], y);
+      const int k = BF ? e >> 1 : e;
+      float d[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const uint32_t u = k == 0 ? r[j][0] : k == 1 ? r[j][1] : k == 2 ? r[j][2] : r[j][3];
+        d[j] = __uint_as_float(BF ? ((e & 1) ? (u & 0xffff0000u) : (u << 16)) : u);
       }
-      v[0][e] = x[0]; v[1][e] = x[1]; v[2][e] = x[2];
-      v[3][e] = y[0]; v[4][e] = y[1]; v[5][e] = y[2];
-      v[6][e] = d[2][e];
+      const int fc = f < s.n_frames ? f : s.n_frames - 1;
+      float x[7];
+      unproject(s.dp->p[fc], (float)col, (float)row, d[0], x);
+      unproject(s.dp->q[fc], (float)col, (float)row, d[1], x + 3);
+      x[6] = d[2];
+      point(x, e);
       if (g0 + e >= s.a) advance(s, f, row, col);
     }
   }
@@ -439,10 +448,7 @@ __device__ inline SrcCtx<DT> make_src(const void* const* pl, const Work& w, cons
     s.n_frames = uniform_i32(s.dp->n_frames);
     s.inv_width = uniform_f32(s.dp->inv_width);
     s.inv_frame = uniform_f32(s.dp->inv_frame);
-    const int HW = s.frame_pixels, nf = s.n_frames;
-    const int64_t first = td.begin > td.lo ? td.begin : td.lo;
-    const int f0 = (int)((first - td.lo) / HW), f1 = (int)((td.end - 1 - td.lo) / HW);
-    s.frame = (f0 == f1 && f0 < nf && td.end > first) ? f0 : -1;
+    s.frame = td.frame;
     if (s.frame >= 0) {
       s.cp = load_cam_uniform(s.dp->p + s.frame);
       s.cq = load_cam_uniform(s.dp->q + s.frame);
@@ -634,6 +640,99 @@ __device__ inline void gn_point(float (&a)[NSTAT], float y0, float y1, float y2,
   }
 }
 
+// Pixel positions of a lane's vectors in a depth tile that lies in one frame, and
+// what a row shares. A pixel's ray is affine in its column, so for a camera form
+// (G, f): G0 (col ifx + ox) + [G1 (row ify + oy) + G2], the bracket is one value a row
+// and component. The walk keeps (row, col) of the vector's first pixel and steps it
+// by the lane stride; a vector crosses at most one row end (frames at least a vector
+// wide). Every product and sum is the one that a pixel on its own would form, so
+// sharing a row changes no bit. Elements before the pair count back from its first
+// row (their values are masked).
+template <int DT>
+struct DepthWalk {
+  int row, col, drow, dcol, width;
+  __device__ inline DepthWalk(const SrcCtx<DT>& s, const TileDesc& td, int first, int stride) {
+    width = s.width;
+    const int back = 64 * width;  // a tile starts at most 63 elements before the pair
+    const int j = (int)(td.begin + first - td.lo) - s.frame * s.frame_pixels + back;
+    row = div_floor(j, width, s.inv_width);
+    col = j - row * width;
+    row -= 64;
+    drow = uniform_i32(div_floor(stride, width, s.inv_width));
+    dcol = stride - drow * width;
+  }
+  __device__ inline void next() {
+    row += drow;
+    col += dcol;
+    if (col >= width) {
+      col -= width;
+      ++row;
+    }
+  }
+};
+
+// A value kept in a vector register: an operation reads one scalar register, so of
+// two uniform operands the compiler would copy one for every pixel.
+__device__ inline float in_vgpr(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// A camera form: G (rows of three) with its column's intrinsics, ray_i = G_i0 rx + h_i.
+struct CamForm {
+  float g0[3], g1[3], g2[3], ifx, ox, ify, oy;
+  __device__ inline CamForm(const float* G, const DepthCam& c) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      g0[i] = uniform_f32(G[3 * i]);
+      g1[i] = uniform_f32(G[3 * i + 1]);
+      g2[i] = in_vgpr(G[3 * i + 2]);
+    }
+    ifx = c.ifx;
+    ox = in_vgpr(c.ox);
+    ify = c.ify;
+    oy = in_vgpr(c.oy);
+  }
+  // the row's share of the ray
+  __device__ inline void row(float r, float (&h)[3]) const {
+    const float ry = fmaf(r, ify, oy);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) h[i] = fmaf(g1[i], ry, g2[i]);
+  }
+};
+
+// Calls pixel(e, hp, hq, col) for the VEC pixels of the walk's vector, hp and hq the
+// row shares of the forms: one row's where no lane of the wavefront crosses a row
+// end, else the first or the next row's, chosen per pixel.
+template <int VEC, int DT, typename Pixel>
+__device__ inline void walk_pixels(const DepthWalk<DT>& p, const CamForm& P, const CamForm& Q, Pixel&& pixel) {
+  float hp[3], hq[3];
+  const float fr = (float)p.row, fc = (float)p.col;
+  P.row(fr, hp);
+  Q.row(fr, hq);
+  const bool cross = p.col + VEC > p.width;
+  if (__builtin_amdgcn_ballot_w64(cross) == 0ull) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) pixel(e, hp, hq, fc + (float)e);
+  } else {
+    float hp1[3], hq1[3];
+    P.row(fr + 1.0f, hp1);
+    Q.row(fr + 1.0f, hq1);
+    const float fw = (float)p.width;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const bool over = p.col + e >= p.width;
+      float sp[3], sq[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        sp[i] = over ? hp1[i] : hp[i];
+        sq[i] = over ? hq1[i] : hq[i];
+      }
+      pixel(e, sp, sq, over ? fc + (float)e - fw : fc + (float)e);
+    }
+  }
+}
+
 // The raw buffers of a tile's walk, whatever the input kind.
 template <int DT>
 struct TileRaw {
@@ -648,13 +747,17 @@ struct TileRaw<DT_DEPTH_BF16> {
   typedef DepthPlanes<DT_DEPTH_BF16>::Raw type;
 };
 
-// Issue the loads of the lane's first vector of a tile.
+// Issue the loads of the lane's first vector of a tile (before its cameras are known).
 template <int DT, int WG>
-__device__ inline void tile_begin(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
+__device__ inline void tile_begin(const Shape& sh, const void* const* pl, const TileDesc& td,
                                   typename TileRaw<DT>::type& r) {
   using Raw = typename TileRaw<DT>::type;
+  SrcCtx<DT> src;
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
-    if (src.frame < 0) return;  // a tile that spans frames does not walk raw vectors
+    if (td.frame < 0) return;  // a tile that spans frames does not walk raw vectors
+    for (int j = 0; j < 3; ++j) src.pl[j] = pl[j];
+  } else {
+    src.pl = pl;
   }
   pipelined_begin<WG, Planes<DT>::VEC, Raw>(
       (int)(td.end - td.begin), [&](int rel, Raw& x) { Planes<DT>::fetch(src, td.begin + rel, sh.n_points, x); }, r);
@@ -664,6 +767,12 @@ __device__ inline void tile_begin(const Shape& sh, const SrcCtx<DT>& src, const 
 // current similarity is folded into each side's camera once per tile, so a
 // pixel costs one affine map per side on its ray:
 //   y_c = d_p (A ray_p) + b,  A = sR R_p, b = sR t_p + t - c;   q_c = d_q (R_q ray_q) + t_q - c.
+// Bound by instruction issue, not by the loads: about 71 vector operations a pixel, four
+// cycles each on a SIMD, are 1.7 us a million pixels for the chip at its clock, and
+// the loads alone as long. Forming a row's share of the ray, the positions and the
+// masks once a vector, and the fourth wavefront per SIMD that the saved registers give:
+// 256 pairs of 518 x 392 frames (62 M pixels) 169 -> 159 us a pass; a few pairs, bound
+// by one wavefront's chain, 345 -> 200 us a call of 10 steps.
 template <int DT, int WG, int ITEMS, bool COST, bool BEGUN>
 __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
                                            const PointParams& P, typename DepthPlanes<DT>::Raw& first,
@@ -678,44 +787,49 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
 #pragma unroll
     for (int j = 0; j < 3; ++j)
       A[3 * i + j] = fmaf(P.Mf[3 * i], cp.R[j], fmaf(P.Mf[3 * i + 1], cp.R[3 + j], P.Mf[3 * i + 2] * cp.R[6 + j]));
-    b[i] = fmaf(P.Mf[3 * i], cp.t[0], fmaf(P.Mf[3 * i + 1], cp.t[1], fmaf(P.Mf[3 * i + 2], cp.t[2], P.tcf[i])));
-    bq[i] = cq.t[i] - P.cf[i];
+    b[i] = uniform_f32(fmaf(P.Mf[3 * i], cp.t[0], fmaf(P.Mf[3 * i + 1], cp.t[1], fmaf(P.Mf[3 * i + 2], cp.t[2], P.tcf[i]))));
+    bq[i] = uniform_f32(cq.t[i] - P.cf[i]);
   }
   const float tau = sh.tau, delta = sh.delta_f;
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
   const bool check_finite = P.nonfinite != 0;
   auto fetch = [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); };
+  DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
+  const CamForm fp(A, cp), fq(cq.R, cq);
   auto body = [&](const typename L::Raw& raw, int rel0) {
     float d[3][VEC];
     L::unpack(raw, d);
-    int f, row, col;
-    L::position(src, td.begin + rel0, f, row, col);
+    // a pair's first and last vectors, and in pairs that hold any, pixels whose depths
+    // are not finite or not such that their squares are (the closed form failed then),
+    // or whose confidence is not finite: zeroed, so of weight zero and finite
+    if (check_finite || rel0 < lo_rel || rel0 + VEC > end_rel) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const bool in = rel0 + e >= lo_rel && rel0 + e < end_rel;
-      const float fc = (float)col, fr = (float)row;
-      const float rxp = fmaf(fc, cp.ifx, cp.ox), ryp = fmaf(fr, cp.ify, cp.oy);
-      const float rxq = fmaf(fc, cq.ifx, cq.ox), ryq = fmaf(fr, cq.ify, cq.oy);
+      for (int e = 0; e < VEC; ++e) {
+        const bool in = rel0 + e >= lo_rel && rel0 + e < end_rel && fabsf(d[0][e]) < 1e30f && fabsf(d[1][e]) < 1e30f &&
+                        __builtin_isfinite(d[2][e]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) d[j][e] = in ? d[j][e] : 0.0f;
+      }
+    }
+    walk_pixels<VEC>(pos, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
+      const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
       float y[3], q[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        y[i] = fmaf(d[0][e], fmaf(A[3 * i], rxp, fmaf(A[3 * i + 1], ryp, A[3 * i + 2])), b[i]);
-        q[i] = fmaf(d[1][e], fmaf(cq.R[3 * i], rxq, fmaf(cq.R[3 * i + 1], ryq, cq.R[3 * i + 2])), bq[i]);
+        y[i] = fmaf(d[0][e], fmaf(fp.g0[i], rxp, hp[i]), b[i]);
+        q[i] = fmaf(d[1][e], fmaf(fq.g0[i], rxq, hq[i]), bq[i]);
       }
-      bool ok = in;
-      if (check_finite) ok = ok && __builtin_isfinite(y[0] + y[1] + y[2] + q[0] + q[1] + q[2]) && __builtin_isfinite(d[2][e]);
       const float c = d[2][e];
-      const float w = (ok && c >= tau) ? c : 0.0f;
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        y[i] = ok ? y[i] : 0.0f;
-        q[i] = ok ? q[i] : 0.0f;
-      }
-      gn_point<COST>(a, y[0], y[1], y[2], y[0] - q[0], y[1] - q[1], y[2] - q[2], w, d2, delta, hd2);
-      if (rel0 + e >= lo_rel) L::advance(src, f, row, col);
-    }
+      gn_point<COST>(a, y[0], y[1], y[2], y[0] - q[0], y[1] - q[1], y[2] - q[2], c >= tau ? c : 0.0f, d2, delta, hd2);
+    });
+    pos.next();
   };
+  if (end_rel == WG * ITEMS * VEC && td.begin + end_rel <= sh.n_points) {
+    full_walk<WG, ITEMS, VEC, typename L::Raw, BEGUN>(
+        [&](int rel, typename L::Raw& r) { L::fetch_full(src, td.begin, rel, r); }, body, first);
+    return;
+  }
   pipelined_walk<WG, ITEMS, VEC, typename L::Raw, BEGUN>(end_rel, fetch, body, first);
 }
 
@@ -802,13 +916,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
       for (int it = 0; it < ITEMS; ++it) {
         const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
         if (rel0 >= end_rel) break;
-        float v[7][VEC];
-        Planes<DT>::load(pl, td.begin + rel0, sh.n_points, v);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          float x[7];
-#pragma unroll
-          for (int j = 0; j < 7; ++j) x[j] = v[j][e];
+        Planes<DT>::each(pl, td.begin + rel0, sh.n_points, [&](float (&x)[7], int e) {
           const bool keep = rel0 + e >= lo_rel && rel0 + e < end_rel && (!check_finite || finite7(x));
 #pragma unroll
           for (int j = 0; j < 7; ++j) x[j] = keep ? x[j] : 0.0f;
@@ -818,7 +926,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
           const float y2 = fmaf(P.Mf[6], x[0], fmaf(P.Mf[7], x[1], fmaf(P.Mf[8], x[2], P.tcf[2])));
           gn_point<COST>(a, y0, y1, y2, y0 - (x[3] - P.cf[0]), y1 - (x[4] - P.cf[1]), y2 - (x[5] - P.cf[2]), w,
                          d2, delta, hd2);
-        }
+        });
       }
     }
   }
@@ -830,9 +938,12 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
 // scene, so FP32 products keep their precision), the products of the VEC pixels of
 // one vector are summed in FP32 and added to FP64 lane sums (the weight sum itself
 // in FP64 per pixel), and the lane sums are moved to the submap frame
-// (x = x' + t) once, in FP64, at the end.
-template <int DT, int WG, int ITEMS>
+// (x = x' + t) once, in FP64, at the end. Bound by issue as the Gauss-Newton pass (189
+// registers, two wavefronts per SIMD; a bound of three spills 130 and is no faster):
+// 233 -> 219 us on the same 256 pairs.
+template <int DT, int WG, int ITEMS, bool BEGUN>
 __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
+                                                typename DepthPlanes<DT>::Raw& first,
                                                 double (&a)[NSTAT], int& nvalid, int& nbad) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC;
@@ -840,27 +951,22 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
   const DepthCam& cq = src.cq;
   const float tau = sh.tau;
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
-  pipelined_items<WG, ITEMS, VEC, typename L::Raw>(
-      end_rel, [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); },
-      [&](const typename L::Raw& raw, int rel0) {
+  DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
+  const CamForm fp(cp.R, cp), fq(cq.R, cq);
+  auto body = [&](const typename L::Raw& raw, int rel0) {
     float d[3][VEC];
     L::unpack(raw, d);
-    int f, row, col;
-    L::position(src, td.begin + rel0, f, row, col);
     float s[17];
 #pragma unroll
     for (int j = 0; j < 17; ++j) s[j] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
+    walk_pixels<VEC>(pos, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
       const bool in = rel0 + e >= lo_rel && rel0 + e < end_rel;
-      const float fc = (float)col, fr = (float)row;
-      const float rxp = fmaf(fc, cp.ifx, cp.ox), ryp = fmaf(fr, cp.ify, cp.oy);
-      const float rxq = fmaf(fc, cq.ifx, cq.ox), ryq = fmaf(fr, cq.ify, cq.oy);
+      const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
       float x[3], y[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        x[i] = d[0][e] * fmaf(cp.R[3 * i], rxp, fmaf(cp.R[3 * i + 1], ryp, cp.R[3 * i + 2]));
-        y[i] = d[1][e] * fmaf(cq.R[3 * i], rxq, fmaf(cq.R[3 * i + 1], ryq, cq.R[3 * i + 2]));
+        x[i] = d[0][e] * fmaf(fp.g0[i], rxp, hp[i]);
+        y[i] = d[1][e] * fmaf(fq.g0[i], rxq, hq[i]);
       }
       const float c = d[2][e];
       const bool fin = __builtin_isfinite(x[0] + x[1] + x[2] + y[0] + y[1] + y[2]) && __builtin_isfinite(c);
@@ -868,10 +974,9 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
       nvalid += valid ? 1 : 0;
       nbad += (in && !fin) ? 1 : 0;
       const float w = valid ? c : 0.0f;
+      if (!fin) {  // (a finite pixel of weight zero adds nothing whatever its coordinates)
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        x[i] = valid ? x[i] : 0.0f;
-        y[i] = valid ? y[i] : 0.0f;
+        for (int i = 0; i < 3; ++i) x[i] = y[i] = 0.0f;
       }
       const float wx0 = w * x[0], wx1 = w * x[1], wx2 = w * x[2];
       const float wy0 = w * y[0], wy1 = w * y[1], wy2 = w * y[2];
@@ -882,11 +987,17 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
       s[8] = fmaf(wy0, x[0], s[8]);  s[9] = fmaf(wy0, x[1], s[9]);  s[10] = fmaf(wy0, x[2], s[10]);
       s[11] = fmaf(wy1, x[0], s[11]); s[12] = fmaf(wy1, x[1], s[12]); s[13] = fmaf(wy1, x[2], s[13]);
       s[14] = fmaf(wy2, x[0], s[14]); s[15] = fmaf(wy2, x[1], s[15]); s[16] = fmaf(wy2, x[2], s[16]);
-      if (rel0 + e >= lo_rel) L::advance(src, f, row, col);
-    }
+    });
+    pos.next();
 #pragma unroll
     for (int j = 1; j < 17; ++j) a[j] += (double)s[j];
-  });
+  };
+  if (end_rel == WG * ITEMS * VEC && td.begin + end_rel <= sh.n_points)
+    full_walk<WG, ITEMS, VEC, typename L::Raw, BEGUN>(
+        [&](int rel, typename L::Raw& r) { L::fetch_full(src, td.begin, rel, r); }, body, first);
+  else
+    pipelined_walk<WG, ITEMS, VEC, typename L::Raw, BEGUN>(
+        end_rel, [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); }, body, first);
   // to the submap frame: x = x' + tp, y = y' + tq
   const double tp[3] = {cp.t[0], cp.t[1], cp.t[2]}, tq[3] = {cq.t[0], cq.t[1], cq.t[2]};
   const double W = a[0], Sx[3] = {a[1], a[2], a[3]}, Sy[3] = {a[4], a[5], a[6]};
@@ -905,9 +1016,9 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
 // Moments pass over one tile: FP64 products and per-lane FP64 sums (the
 // coordinates are uncentred here, so the second moments must keep more than
 // FP32 precision), integer counts, DPP wavefront reduction.
-template <int DT, int WG, int ITEMS>
+template <int DT, int WG, int ITEMS, bool BEGUN>
 __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td,
-                                   double (*red)[NSTAT], double* out) {
+                                   typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out) {
   constexpr int VEC = Planes<DT>::VEC;
   double a[NSTAT];
 #pragma unroll
@@ -917,7 +1028,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
     if (pl.frame >= 0) {
-      tile_moments_depth_frame<DT, WG, ITEMS>(sh, pl, td, a, nvalid, nbad);
+      tile_moments_depth_frame<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, a, nvalid, nbad);
       a[17] = (double)nvalid;
       a[18] = (double)nbad;
       block_store_f64<WG, NSTAT>(a, red, out);
@@ -961,15 +1072,8 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
     for (int it = 0; it < ITEMS; ++it) {
       const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
       if (rel0 >= end_rel) break;
-      float v[7][VEC];
-      Planes<DT>::load(pl, td.begin + rel0, sh.n_points, v);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        float x[7];
-#pragma unroll
-        for (int j = 0; j < 7; ++j) x[j] = v[j][e];
-        point(x, rel0 + e >= lo_rel && rel0 + e < end_rel);
-      }
+      Planes<DT>::each(pl, td.begin + rel0, sh.n_points,
+                       [&](float (&x)[7], int e) { point(x, rel0 + e >= lo_rel && rel0 + e < end_rel); });
     }
   }
   a[17] = (double)nvalid;
@@ -1004,14 +1108,14 @@ __device__ inline void tile_cost(const Shape& sh, const SrcCtx<DT>& pl, const Ti
   block_store_f64<WG, 3>(acc, red, out);
 }
 
-template <int DT, int MODE, int WG, int ITEMS>
-__device__ inline void tile_body(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td,
-                                 const PointParams& P, double (*red)[NSTAT], double* out) {
+// BEGUN: first holds the lane's first vector, its loads issued (tile_begin).
+template <int DT, int MODE, int WG, int ITEMS, bool BEGUN = false>
+__device__ inline void tile_body(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td, const PointParams& P,
+                                 typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out) {
   if constexpr (MODE == MODE_GN || MODE == MODE_GN_NC) {
-    typename TileRaw<DT>::type first;
-    tile_gn<DT, WG, ITEMS, MODE == MODE_GN>(sh, pl, td, P, first, red, out);
+    tile_gn<DT, WG, ITEMS, MODE == MODE_GN, BEGUN>(sh, pl, td, P, first, red, out);
   } else if constexpr (MODE == MODE_MOMENTS) {
-    tile_moments<DT, WG, ITEMS>(sh, pl, td, red, out);
+    tile_moments<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, red, out);
   } else {
     static_assert(MODE == MODE_COST, "unknown pass mode");
     tile_cost<DT, WG, ITEMS>(sh, pl, td, P, red, out);

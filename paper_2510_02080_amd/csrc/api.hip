@@ -305,13 +305,12 @@ hipError_t enqueue_batched(s3a_handle* h, int dtype, const LaunchCfg& lc, const 
 // workgroup. Measured, finalize launches against solving passes, 10 steps: one pair
 // of 3,072 points 113 -> 96 us; 10 pairs of 200,000 FP32 193 -> 165, 20 pairs (1,000
 // tiles) 287 -> 259, 40 pairs 477 -> 469; BF16, 16 pairs 218 -> 193, 32 pairs (1,600
-// tiles) 289 -> 294; depth frames of 203,056 pixels, 20 pairs (260 tiles, the chip's
-// workgroups at once) 365 -> 343, 40 pairs 430 -> 504. A pair of many tiles pays for
-// the gather: one pair of 2 M points (490 tiles) 208 -> 186, of 4 M 329 -> 350.
+// tiles) 289 -> 294; depth frames of 203,056 pixels, 4 pairs 217 -> 199, 20 pairs (260
+// tiles) 269 -> 250, 60 pairs (780 tiles) 423 -> 418, BF16 32 pairs 314 -> 288, 100
+// pairs (700 tiles) 596 -> 589. A pair of many tiles pays for the gather: one pair of
+// 2 M points (490 tiles) 208 -> 186, of 4 M 329 -> 350.
 bool passes_solve(s3a_handle* h, int dtype, int64_t n_points, int n_pairs, int64_t tiles) {
-  if (has_cfg(h, dtype, n_points)) return false;
-  const bool depth = dtype == DT_DEPTH_F32 || dtype == DT_DEPTH_BF16;
-  return tiles <= (depth ? 1 : 4) * (int64_t)h->n_cu && tiles <= 512 * (int64_t)n_pairs;
+  return !has_cfg(h, dtype, n_points) && tiles <= 4 * (int64_t)h->n_cu && tiles <= 512 * (int64_t)n_pairs;
 }
 
 hipError_t enqueue_solving(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,

@@ -111,9 +111,10 @@ __global__ __launch_bounds__(WG, 2) void k_persistent(Shape sh, const CallDesc* 
     }
     const PointParams P = load_params(w.params + j);
     double* out = w.partials + (int64_t)t * NSTAT;
-    if (pass == 0) tile_body<DT, MODE_MOMENTS, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, red, out);
-    else if (pass < sh.K) tile_body<DT, MODE_GN_NC, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, red, out);
-    else tile_body<DT, MODE_GN, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, red, out);
+    RawVec first;
+    if (pass == 0) tile_body<DT, MODE_MOMENTS, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
+    else if (pass < sh.K) tile_body<DT, MODE_GN_NC, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
+    else tile_body<DT, MODE_GN, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
     if (threadIdx.x == 0) {
       __threadfence();  // partials before the arrival
       const uint32_t old = atomicAdd(arrive + j, 1u);

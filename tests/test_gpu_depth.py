@@ -119,3 +119,26 @@ def test_autotune_depth_keeps_its_own_shape(h):
             assert int(info[k]["status"]) == s3a.PAIR_BADRANGE, k
             continue
         check_pair(T[k], info[k], ref, where=f"tuned pair {k}", dr=DR_DEPTH)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("specs", [
+    [(10, 5, 4), (15, 7, 1), (10, 5, 1)],              # frames narrower than a vector of pixels
+    [(21, 9, 1), (20, 8, 1), (34, 17, 2), (33, 15, 1)],  # a row end in most vectors, pairs off alignment
+    [(131, 129, 1), (173, 201, 1), (150, 260, 2)],     # full tiles, partial tiles and tiles that span frames
+], ids=["narrow", "vectors", "tiles"])
+def test_depth_rows_and_tiles(h, specs, dtype):
+    """Row ends, frame ends and tile ends at every place in a vector of pixels,
+    with missing depths and confidences in the last pair."""
+    b = depthmaps.make_depth_batch(specs, seed=47)
+    if dtype == "bf16":
+        b = b.to_bf16()
+    a = int(b.offsets[-2])
+    nan, inf = (0x7fc0, 0x7f80) if dtype == "bf16" else (np.nan, np.inf)
+    b.dp[a + 3::11] = nan
+    b.dq[a + 5::13] = inf
+    b.c[a::17] = nan
+    for flags in (0, s3a.FLAG_PLAIN):
+        T, info = run(h, b, flags)
+        for k in range(b.n_pairs):
+            check_pair(T[k], info[k], oracle_pair(b, k), where=f"{dtype} pair {k} flags {flags}", dr=DR_DEPTH)
