@@ -110,13 +110,10 @@ __global__ __launch_bounds__(64) void k_finalize_adjoint(Shape sh, const CallDes
   double g[7];
   for (int i = 0; i < 7; ++i) g[i] = f * s[i];
   if (cd->xi) {
-    double J[49];
-    sim3_jacobian(cd->xi + 7 * k, 1.0, J);
-    for (int i = 0; i < 7; ++i) {
-      double v = 0.0;
-      for (int m = 0; m < 7; ++m) v += J[7 * m + i] * g[m];
-      out[i] = v;
-    }
+    double xi[7], v[7];
+    for (int i = 0; i < 7; ++i) xi[i] = cd->xi[7 * k + i];
+    sim3_jacobian_t_apply(xi, g, v);
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
   } else {
     for (int i = 0; i < 7; ++i) out[i] = g[i];
   }

@@ -575,6 +575,41 @@ S3A_HD void sim3_jacobian(const double* xi, double sgn, double* J) {
   }
 }
 
+// out = J_l(xi)^T g, the same series applied to the vector: sum (ad(xi)^T)^n g / (n+1)!.
+// With g = (a, b, c) in blocks of 3, 3 and 1, ad(xi)^T g = (a x w + sigma a,
+// a x rho + b x w, -rho . a). It ends when a term is below 1e-18 of the sum's scale and
+// the terms after it shrink at least by half. A term is one short chain of operations
+// (the matrix series multiplies 7 x 7 matrices, and one lane did so for 32 us).
+S3A_HD void sim3_jacobian_t_apply(const double* xi, const double* g, double* out) {
+  const double* rho = xi;
+  const double* w = xi + 3;
+  const double sg = xi[6];
+  double a[3] = {g[0], g[1], g[2]}, b[3] = {g[3], g[4], g[5]}, c = g[6];
+  double big = 0.0, size = fabs(sg);
+  for (int i = 0; i < 7; ++i) {
+    out[i] = g[i];
+    big = fmax(big, fabs(g[i]));
+  }
+  for (int i = 0; i < 3; ++i) size += fabs(w[i]) + fabs(rho[i]);  // bounds ad(xi)^T in the largest-entry norm
+  for (int n = 1; n < 80; ++n) {
+    const double f = (double)(n + 1);
+    const double a0 = (a[1] * w[2] - a[2] * w[1] + sg * a[0]) / f;
+    const double a1 = (a[2] * w[0] - a[0] * w[2] + sg * a[1]) / f;
+    const double a2 = (a[0] * w[1] - a[1] * w[0] + sg * a[2]) / f;
+    const double b0 = (a[1] * rho[2] - a[2] * rho[1] + (b[1] * w[2] - b[2] * w[1])) / f;
+    const double b1 = (a[2] * rho[0] - a[0] * rho[2] + (b[2] * w[0] - b[0] * w[2])) / f;
+    const double b2 = (a[0] * rho[1] - a[1] * rho[0] + (b[0] * w[1] - b[1] * w[0])) / f;
+    c = -(a[0] * rho[0] + a[1] * rho[1] + a[2] * rho[2]) / f;
+    a[0] = a0; a[1] = a1; a[2] = a2;
+    b[0] = b0; b[1] = b1; b[2] = b2;
+    out[0] += a0; out[1] += a1; out[2] += a2;
+    out[3] += b0; out[4] += b1; out[5] += b2;
+    out[6] += c;
+    const double mx = fmax(fmax(fmax(fabs(a0), fabs(a1)), fmax(fabs(a2), fabs(c))), fmax(fabs(b0), fmax(fabs(b1), fabs(b2))));
+    if (mx <= 1e-18 * big && 2.0 * size <= (double)(n + 2)) break;
+  }
+}
+
 // Gauss-Jordan inverse with partial pivoting (n = 7). Returns false if singular.
 S3A_HD bool inv7(const double* A, double* X) {
   double M[7 * 14];

@@ -36,6 +36,7 @@ void s3a_host_sim3_ad(const double* xi, double* A) { sim3_ad(xi, A); }
 void s3a_host_sim3_Ad(const double* T, double* A) { sim3_Ad(load(T), A); }
 
 void s3a_host_sim3_jacobian(const double* xi, double sgn, double* J) { sim3_jacobian(xi, sgn, J); }
+void s3a_host_sim3_jacobian_t_apply(const double* xi, const double* g, double* out) { sim3_jacobian_t_apply(xi, g, out); }
 
 int s3a_host_inv7(const double* A, double* X) { return inv7(A, X) ? 0 : 1; }
 

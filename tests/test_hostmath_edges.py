@@ -68,3 +68,27 @@ def test_umeyama_second_singular_value(lib, ratio, ok):
     if ok:
         # U V^T; the eigenvector's error is the rounding of M over the gap of its quaternion form
         assert np.abs(T[:9].reshape(3, 3) - U @ V.T).max() <= 1e-14 / ratio
+
+
+@pytest.mark.parametrize("xi", [
+    np.zeros(7), [0, 0, 0, 0, 0, 0, 0.5], [0.4, -2.0, 1.0, 0, 0, 0, 0], [0.3, 0.1, -0.2, 1e-9, 0, 0, 1e-9],
+    [0.7, -1.3, 0.4, 0.2, -0.1, 0.3, 0.1], [5.0, 8.0, -3.0, 1.9, -1.7, 1.8, -2.0], [20.0, 0, 0, 0, 3.0, 0, 4.0]])
+def test_left_jacobian_transposed_on_a_vector(lib, xi):
+    """J_l(xi)^T g by the vector series against the series in extended precision:
+    roundings of terms that add up to at most e^|ad| times |g|."""
+    xi = np.asarray(xi, dtype=np.float64)
+    hat = lambda v: np.array([[0, -v[2], v[1]], [v[2], 0, -v[0]], [-v[1], v[0], 0]])
+    A = np.zeros((7, 7))
+    A[:3, :3] = hat(xi[3:6]) + xi[6] * np.eye(3)
+    A[:3, 3:6], A[3:6, 3:6], A[:3, 6] = hat(xi[:3]), hat(xi[3:6]), -xi[:3]
+    A = A.T.astype(np.longdouble)
+    for g in list(np.eye(7)) + [np.random.default_rng(3).normal(size=7)]:
+        term, want, size = g.astype(np.longdouble), g.astype(np.longdouble), np.abs(g).astype(np.longdouble)
+        mag = size.copy()
+        for n in range(1, 150):
+            term, size = A @ term / (n + 1), np.abs(A) @ size / (n + 1)
+            want, mag = want + term, mag + size
+        out = np.zeros(7)
+        lib.s3a_host_sim3_jacobian_t_apply(dp(xi), dp(np.ascontiguousarray(g)), dp(out))
+        # term n carries at most 8 roundings a step; the terms that count end by n = 60
+        assert (np.abs(out - want) <= 60 * 8 * 2.0**-53 * mag + 1e-17).all(), (g, out, want)
