@@ -70,6 +70,8 @@ _EXPORTS = {
                                       c_void_p]),
     "s3a_align_pairs_backward": (ctypes.c_int, [c_void_p, ctypes.POINTER(AlignDesc), c_void_p, c_void_p, c_void_p,
                                                 c_void_p, c_void_p] + [c_void_p] * 8 + [c_void_p]),
+    "s3a_align_pairs_backward_zeroed": (ctypes.c_int, [c_void_p, ctypes.POINTER(AlignDesc), c_void_p, c_void_p, c_void_p,
+                                                       c_void_p, c_void_p] + [c_void_p] * 8 + [c_void_p]),
     "s3a_pose_graph_solve": (ctypes.c_int, [c_void_p, ctypes.c_int32, ctypes.c_int32, c_void_p, c_void_p, c_void_p,
                                             c_void_p, ctypes.POINTER(PgoParams), ctypes.POINTER(PgoReport), c_void_p]),
     "s3a_autotune": (ctypes.c_int, [c_void_p, ctypes.POINTER(AlignDesc), ctypes.POINTER(Tuning), c_void_p]),
@@ -85,6 +87,8 @@ _EXPORTS = {
                                           c_void_p]),
     "s3a_align_pairs_implicit_backward": (ctypes.c_int, [c_void_p, ctypes.POINTER(AlignDesc), c_void_p, c_void_p,
                                                          ctypes.c_uint32] + [c_void_p] * 9 + [c_void_p]),
+    "s3a_align_pairs_implicit_backward_zeroed": (ctypes.c_int, [c_void_p, ctypes.POINTER(AlignDesc), c_void_p, c_void_p,
+                                                                ctypes.c_uint32] + [c_void_p] * 9 + [c_void_p]),
     "s3a_align_depth_pairs": (ctypes.c_int, [c_void_p, ctypes.POINTER(DepthDesc), c_void_p, c_void_p, c_void_p,
                                              c_void_p]),
     "s3a_edges_from_alignment": (ctypes.c_int, [c_void_p, ctypes.c_int32, c_void_p, c_void_p, ctypes.c_double,
@@ -141,8 +145,8 @@ class Pointmaps:
 
     def __init__(self, planes, offsets, dtype, covers_all=False):
         """covers_all: the caller asserts that the offsets are non-decreasing
-        from 0 to N (every stored point belongs to a pair), so gradient
-        buffers need no zeroing outside the pairs."""
+        from 0 to N (every stored point belongs to a pair). The gradient
+        calls no longer need to know: they write zeros outside the pairs."""
         assert len(planes) == 7
         self.planes = list(planes)
         self.offsets = offsets
@@ -286,8 +290,9 @@ class Handle:
         N = pm.n_points
         Np = (N + 3) // 4 * 4  # row stride keeping every plane 16-byte aligned
         dev = pm.device
-        # the library writes every entry inside the pairs; the rest is zeroed here
-        alloc = torch.empty if pm.covers_all else torch.zeros
+        # the library writes every entry: those inside the pairs, and zeros outside (a
+        # call without pairs writes nothing)
+        alloc = torch.empty if pm.n_pairs else torch.zeros
         gp = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
         gq = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
         gc = alloc(N, dtype=torch.float32, device=dev) if need[2] else None
@@ -295,8 +300,8 @@ class Handle:
         d = pm.desc(tau, delta, 0)
         gps = [_ptr(gp[i]) if gp is not None else None for i in range(3)]
         gqs = [_ptr(gq[i]) if gq is not None else None for i in range(3)]
-        _check(self.lib.s3a_align_pairs_backward(self.h, ctypes.byref(d), _ptr(S), _ptr(xi), _ptr(L), _ptr(C),
-                                                 _ptr(gL), *gps, *gqs, _ptr(gc), _ptr(gxi), _stream(dev)), self.h)
+        _check(self.lib.s3a_align_pairs_backward_zeroed(self.h, ctypes.byref(d), _ptr(S), _ptr(xi), _ptr(L), _ptr(C),
+                                                        _ptr(gL), *gps, *gqs, _ptr(gc), _ptr(gxi), _stream(dev)), self.h)
         return gp, gq, gc, gxi
 
     def align_pairs_implicit_backward(self, pm, S, gS, tau, delta=0.05, tangent=False, need=(True, True, True)):
@@ -308,7 +313,7 @@ class Handle:
         N = pm.n_points
         Np = (N + 3) // 4 * 4
         dev = pm.device
-        alloc = torch.empty if pm.covers_all else torch.zeros
+        alloc = torch.empty if pm.n_pairs else torch.zeros
         gp = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
         gq = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
         gc = alloc(N, dtype=torch.float32, device=dev) if need[2] else None
@@ -317,9 +322,9 @@ class Handle:
         d = pm.desc(tau, delta, 0)
         gps = [_ptr(gp[i]) if gp is not None else None for i in range(3)]
         gqs = [_ptr(gq[i]) if gq is not None else None for i in range(3)]
-        _check(self.lib.s3a_align_pairs_implicit_backward(self.h, ctypes.byref(d), _ptr(S), _ptr(gS),
-                                                          IMPLICIT_TANGENT if tangent else 0, *gps, *gqs, _ptr(gc),
-                                                          _ptr(v), _ptr(status), _stream(dev)), self.h)
+        _check(self.lib.s3a_align_pairs_implicit_backward_zeroed(
+            self.h, ctypes.byref(d), _ptr(S), _ptr(gS), IMPLICIT_TANGENT if tangent else 0, *gps, *gqs, _ptr(gc),
+            _ptr(v), _ptr(status), _stream(dev)), self.h)
         return gp, gq, gc, v, status
 
     def pose_graph_solve(self, edges, T_meas, T=None, omega=None, iters=20, huber_delta=float("inf"),

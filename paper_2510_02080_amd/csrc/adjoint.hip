@@ -90,6 +90,7 @@ __global__ __launch_bounds__(WG) void k_adjoint(Shape sh, const CallDesc* __rest
     }
     block_store_f64<WG, 7>(acc, red, w.partials + (int64_t)t * NSTAT);
   }
+  zero_rest(sh, w, gout);
 }
 
 // dL/dxi = gL J_l(xi)^T (1/C) sum om J^T r.

@@ -654,7 +654,7 @@ int s3a_align_cost(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, co
   return S3A_OK;
 }
 
-int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, const double* xi,
+static int backward_impl(s3a_handle* h, bool zero_rest, const s3a_align_desc* d, const s3a_sim3* S, const double* xi,
                              const double* L, const double* C, const double* gL, float* gpx, float* gpy, float* gpz,
                              float* gqx, float* gqy, float* gqz, float* gc, double* gxi, s3a_stream stream) {
   if (!h) return S3A_EINVAL;
@@ -669,7 +669,8 @@ int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_s
   hipStream_t st = static_cast<hipStream_t>(stream);
   S3A_ORDERED(h, st);
   const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
-  const Shape sh = make_shape(d, lc);
+  Shape sh = make_shape(d, lc);
+  if (zero_rest) sh.flags |= SHAPE_ZERO_REST;
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
   if (mt >= (1ll << 31)) return S3A_EINVAL;
   rc = ensure_workspace(h, d->n_pairs, mt);
@@ -693,7 +694,7 @@ int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_s
   return S3A_OK;
 }
 
-int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, const double* gS,
+static int implicit_backward_impl(s3a_handle* h, bool zero_rest, const s3a_align_desc* d, const s3a_sim3* S, const double* gS,
                                       uint32_t iflags, float* gpx, float* gpy, float* gpz, float* gqx, float* gqy,
                                       float* gqz, float* gc, double* v_out, int32_t* status_out, s3a_stream stream) {
   if (!h) return S3A_EINVAL;
@@ -709,7 +710,8 @@ int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* d, co
   hipStream_t st = static_cast<hipStream_t>(stream);
   S3A_ORDERED(h, st);
   const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
-  const Shape sh = make_shape(d, lc);
+  Shape sh = make_shape(d, lc);
+  if (zero_rest) sh.flags |= SHAPE_ZERO_REST;
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
   if (mt >= (1ll << 31)) return S3A_EINVAL;
   rc = ensure_workspace(h, d->n_pairs, mt);
@@ -736,6 +738,32 @@ int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* d, co
   S3A_TRY(launch_implicit(d->dtype, lc, sh, dcd, h->w, h->hpart, gS, iflags, v_out, status_out, grid_for(h, lc, mt), mt,
                           h->n_cu, st));
   return S3A_OK;
+}
+
+int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, const double* xi,
+                             const double* L, const double* C, const double* gL, float* gpx, float* gpy, float* gpz,
+                             float* gqx, float* gqy, float* gqz, float* gc, double* gxi, s3a_stream stream) {
+  return backward_impl(h, false, d, S, xi, L, C, gL, gpx, gpy, gpz, gqx, gqy, gqz, gc, gxi, stream);
+}
+
+int s3a_align_pairs_backward_zeroed(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, const double* xi,
+                                    const double* L, const double* C, const double* gL, float* gpx, float* gpy,
+                                    float* gpz, float* gqx, float* gqy, float* gqz, float* gc, double* gxi,
+                                    s3a_stream stream) {
+  return backward_impl(h, true, d, S, xi, L, C, gL, gpx, gpy, gpz, gqx, gqy, gqz, gc, gxi, stream);
+}
+
+int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, const double* gS,
+                                      uint32_t iflags, float* gpx, float* gpy, float* gpz, float* gqx, float* gqy,
+                                      float* gqz, float* gc, double* v_out, int32_t* status_out, s3a_stream stream) {
+  return implicit_backward_impl(h, false, d, S, gS, iflags, gpx, gpy, gpz, gqx, gqy, gqz, gc, v_out, status_out, stream);
+}
+
+int s3a_align_pairs_implicit_backward_zeroed(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S,
+                                             const double* gS, uint32_t iflags, float* gpx, float* gpy, float* gpz,
+                                             float* gqx, float* gqy, float* gqz, float* gc, double* v_out,
+                                             int32_t* status_out, s3a_stream stream) {
+  return implicit_backward_impl(h, true, d, S, gS, iflags, gpx, gpy, gpz, gqx, gqy, gqz, gc, v_out, status_out, stream);
 }
 
 int s3a_set_timing(s3a_handle* h, int on) {

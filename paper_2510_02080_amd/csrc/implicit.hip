@@ -497,6 +497,7 @@ __global__ __launch_bounds__(WG) void k_igrad(Shape sh, const CallDesc* __restri
       for (int j = 0; j < 7; ++j) store_grad_vec(gout[j], g0, sh.n_points, go[j], VEC, td.lo, td.end);
     }
   }
+  zero_rest(sh, w, gout);
 }
 
 // Workgroups of a kernel that one compute unit holds at once (at least 1).

@@ -128,6 +128,9 @@ struct CallDesc {
   const s3a_depth_pair* depth;  // caller's per-pair cameras (depth input), or null
 };
 
+// Internal bit of Shape::flags beside the caller's S3A_FLAG_*: see zero_rest.
+constexpr uint32_t SHAPE_ZERO_REST = 0x80000000u;
+
 // Shape of a call (passed by value).
 struct Shape {
   int64_t n_points;
