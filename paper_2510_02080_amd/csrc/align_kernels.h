@@ -717,16 +717,16 @@ struct CamForm {
   }
 };
 
-// Calls pixel(e, hp, hq, col) for the VEC pixels of the walk's vector, hp and hq the
+// Calls pixel(e, hp, hq, col) for the VEC pixels from (row, col), hp and hq the
 // row shares of the forms: one row's where no lane of the wavefront crosses a row
 // end, else the first or the next row's, chosen per pixel.
-template <int VEC, int DT, typename Pixel>
-__device__ inline void walk_pixels(const DepthWalk<DT>& p, const CamForm& P, const CamForm& Q, Pixel&& pixel) {
+template <int VEC, typename Pixel>
+__device__ inline void walk_pixels(int row, int col, int width, const CamForm& P, const CamForm& Q, Pixel&& pixel) {
   float hp[3], hq[3];
-  const float fr = (float)p.row, fc = (float)p.col;
+  const float fr = (float)row, fc = (float)col;
   P.row(fr, hp);
   Q.row(fr, hq);
-  const bool cross = p.col + VEC > p.width;
+  const bool cross = col + VEC > width;
   if (__builtin_amdgcn_ballot_w64(cross) == 0ull) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) pixel(e, hp, hq, fc + (float)e);
@@ -734,10 +734,10 @@ __device__ inline void walk_pixels(const DepthWalk<DT>& p, const CamForm& P, con
     float hp1[3], hq1[3];
     P.row(fr + 1.0f, hp1);
     Q.row(fr + 1.0f, hq1);
-    const float fw = (float)p.width;
+    const float fw = (float)width;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      const bool over = p.col + e >= p.width;
+      const bool over = col + e >= width;
       float sp[3], sq[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -746,6 +746,66 @@ __device__ inline void walk_pixels(const DepthWalk<DT>& p, const CamForm& P, con
       }
       pixel(e, sp, sq, over ? fc + (float)e - fw : fc + (float)e);
     }
+  }
+}
+
+// A depth tile that spans frames: point(x, in) takes (p, q, c) of each element in the
+// pair's submap frames, frame after frame, each lane's elements in order (in: the
+// element lies in the tile, the pair and the frame at hand; a vector that holds a
+// frame's end comes once with each). Frames of a few thousand pixels put every tile
+// here. Bound by issue: with cameras and rows taken per segment instead of per element,
+// 150 pairs of one to three 160 x 120 BF16 frames 722 -> 413 us a call, 60 pairs of
+// 300 x 200 779 -> 475, and 256 pairs of 518 x 392 FP32, whose last tiles these are,
+// 1863 -> 1681. One element at a time remains for frames narrower than a
+// vector, where one may hold several row ends.
+template <int DT, int WG, int ITEMS, typename Point>
+__device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const TileDesc& td, Point&& point) {
+  using L = DepthPlanes<DT>;
+  constexpr int VEC = L::VEC, STRIDE = WG * VEC;
+  const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin), at = (int)(td.begin - s.a);
+  if (s.width < VEC) {
+#pragma unroll 1
+    for (int it = 0; it < ITEMS; ++it) {
+      const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
+      if (rel0 >= end_rel) break;
+      L::each(s, td.begin + rel0, sh.n_points,
+              [&](float (&x)[7], int e) { point(x, rel0 + e >= lo_rel && rel0 + e < end_rel); });
+    }
+    return;
+  }
+  int seg = lo_rel > 0 ? lo_rel : 0;
+#pragma unroll 1
+  while (seg < end_rel) {
+    int f = uniform_i32(div_floor(at + seg, s.frame_pixels, s.inv_frame));
+    f = f < s.n_frames ? f : s.n_frames - 1;
+    const int64_t here = (int64_t)(f + 1) * s.frame_pixels - at;  // where the frame ends
+    const int seg_end = f + 1 < s.n_frames && here < end_rel ? (int)here : end_rel;
+    const DepthCam cp = load_cam_uniform(s.dp->p + f), cq = load_cam_uniform(s.dp->q + f);
+    const CamForm fp(cp.R, cp), fq(cq.R, cq);
+#pragma unroll 1
+    for (int it = seg / STRIDE; it * STRIDE < seg_end; ++it) {
+      const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
+      if (rel0 >= seg_end || rel0 + VEC <= seg) continue;
+      typename L::Raw r;
+      L::fetch(s, td.begin + rel0, sh.n_points, r);
+      float d[3][VEC];
+      L::unpack(r, d);
+      const int j = at + rel0 - f * s.frame_pixels;  // above -VEC: the vector may begin in the frame before
+      const int row = j < 0 ? -1 : div_floor(j, s.width, s.inv_width);
+      walk_pixels<VEC>(row, j - row * s.width, s.width, fp, fq,
+                       [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
+        const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
+        float x[7];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          x[i] = fmaf(d[0][e], fmaf(fp.g0[i], rxp, hp[i]), cp.t[i]);
+          x[3 + i] = fmaf(d[1][e], fmaf(fq.g0[i], rxq, hq[i]), cq.t[i]);
+        }
+        x[6] = d[2][e];
+        point(x, rel0 + e >= seg && rel0 + e < seg_end);
+      });
+    }
+    seg = seg_end;
   }
 }
 
@@ -828,7 +888,7 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
         for (int j = 0; j < 3; ++j) d[j][e] = in ? d[j][e] : 0.0f;
       }
     }
-    walk_pixels<VEC>(pos, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
+    walk_pixels<VEC>(pos.row, pos.col, pos.width, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
       const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
       float y[3], q[3];
 #pragma unroll
@@ -928,22 +988,17 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
       // depth input whose tile spans frames: unprojected per element (DepthPlanes::load)
       const float tau = sh.tau, delta = sh.delta_f;
       const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
-#pragma unroll 1
-      for (int it = 0; it < ITEMS; ++it) {
-        const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
-        if (rel0 >= end_rel) break;
-        Planes<DT>::each(pl, td.begin + rel0, sh.n_points, [&](float (&x)[7], int e) {
-          const bool keep = rel0 + e >= lo_rel && rel0 + e < end_rel && (!check_finite || finite7(x));
+      span_walk<DT, WG, ITEMS>(sh, pl, td, [&](float (&x)[7], bool in) {
+        const bool keep = in && (!check_finite || finite7(x));
 #pragma unroll
-          for (int j = 0; j < 7; ++j) x[j] = keep ? x[j] : 0.0f;
-          const float w = x[6] >= tau ? x[6] : 0.0f;
-          const float y0 = fmaf(P.Mf[0], x[0], fmaf(P.Mf[1], x[1], fmaf(P.Mf[2], x[2], P.tcf[0])));
-          const float y1 = fmaf(P.Mf[3], x[0], fmaf(P.Mf[4], x[1], fmaf(P.Mf[5], x[2], P.tcf[1])));
-          const float y2 = fmaf(P.Mf[6], x[0], fmaf(P.Mf[7], x[1], fmaf(P.Mf[8], x[2], P.tcf[2])));
-          gn_point<COST>(a, y0, y1, y2, y0 - (x[3] - P.cf[0]), y1 - (x[4] - P.cf[1]), y2 - (x[5] - P.cf[2]), w,
-                         d2, delta, hd2);
-        });
-      }
+        for (int j = 0; j < 7; ++j) x[j] = keep ? x[j] : 0.0f;
+        const float w = x[6] >= tau ? x[6] : 0.0f;
+        const float y0 = fmaf(P.Mf[0], x[0], fmaf(P.Mf[1], x[1], fmaf(P.Mf[2], x[2], P.tcf[0])));
+        const float y1 = fmaf(P.Mf[3], x[0], fmaf(P.Mf[4], x[1], fmaf(P.Mf[5], x[2], P.tcf[1])));
+        const float y2 = fmaf(P.Mf[6], x[0], fmaf(P.Mf[7], x[1], fmaf(P.Mf[8], x[2], P.tcf[2])));
+        gn_point<COST>(a, y0, y1, y2, y0 - (x[3] - P.cf[0]), y1 - (x[4] - P.cf[1]), y2 - (x[5] - P.cf[2]), w,
+                       d2, delta, hd2);
+      });
     }
   }
   block_store_f32<WG>(a, red, out);
@@ -975,7 +1030,7 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
     float s[17];
 #pragma unroll
     for (int j = 0; j < 17; ++j) s[j] = 0.0f;
-    walk_pixels<VEC>(pos, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
+    walk_pixels<VEC>(pos.row, pos.col, pos.width, fp, fq, [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
       const bool in = rel0 + e >= lo_rel && rel0 + e < end_rel;
       const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
       float x[3], y[3];
@@ -1084,13 +1139,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
           }
         });
   } else {
-#pragma unroll 1
-    for (int it = 0; it < ITEMS; ++it) {
-      const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
-      if (rel0 >= end_rel) break;
-      Planes<DT>::each(pl, td.begin + rel0, sh.n_points,
-                       [&](float (&x)[7], int e) { point(x, rel0 + e >= lo_rel && rel0 + e < end_rel); });
-    }
+    span_walk<DT, WG, ITEMS>(sh, pl, td, point);
   }
   a[17] = (double)nvalid;
   a[18] = (double)nbad;
