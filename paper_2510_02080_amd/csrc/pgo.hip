@@ -328,16 +328,19 @@ __device__ inline double* target_elem(const PgoDev& d, int target, int lane) {
 // by one wavefront, lane = element (r, s) of the 7x7 block, in list order. The block
 // indices are fetched 64 at a time, one per lane, and read back from lanes (uniform),
 // so the only dependent loads left are the blocks; four updates are in flight.
-// The lane's element is read from `src` and the result written to `dst`.
+// The lane's element is read from `src` and the result written to `dst`. ia, ib: the
+// lane's entries of the list's first 64 (the second form reads them).
 __device__ inline void update_target(const PgoDev& d, const double* src, double* dst, int q0, int q1,
-                                     const int32_t* ua, const int32_t* ub, int lane) {
+                                     const int32_t* ua, const int32_t* ub, int lane, int ia, int ib) {
   const int r = lane < 49 ? lane / 7 : 0, s = lane < 49 ? lane % 7 : 0;
   const double old = *src;  // issued first: its latency overlaps the update loads
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
   for (int qb = q0; qb < q1; qb += 64) {
     const int nq = min(64, q1 - qb);
-    const int ia = lane < nq ? ua[qb + lane] : 0;
-    const int ib = lane < nq ? ub[qb + lane] : 0;
+    if (qb > q0) {
+      ia = lane < nq ? ua[qb + lane] : 0;
+      ib = lane < nq ? ub[qb + lane] : 0;
+    }
     int u = 0;
     for (; u + 4 <= nq; u += 4) {
       const double* A0 = d.Lb + 49 * __shfl(ia, u, 64) + 7 * r;
@@ -366,53 +369,57 @@ __device__ inline void update_target(const PgoDev& d, const double* src, double*
   if (lane < 49) *dst = old - ((acc0 + acc1) + (acc2 + acc3));
 }
 
-// In-place Cholesky of one 7x7 diagonal block by one lane (row by row), zeroing
-// the upper triangle, and the inverse of the factor into Di (and its lower
-// triangle, row by row, to copy[e * cstride] when given): each diagonal element is
-// inverted once, so the triangular solves that use the block need no divisions.
-// False if a pivot is not positive.
-__device__ inline bool chol7_lane(double* D, double* Di, double* copy, int cstride) {
-  double L[7][7];
-  double rinv[7];
+__device__ inline void update_target(const PgoDev& d, const double* src, double* dst, int q0, int q1,
+                                     const int32_t* ua, const int32_t* ub, int lane) {
+  const bool in = q0 + lane < q1;
+  update_target(d, src, dst, q0, q1, ua, ub, lane, in ? ua[q0 + lane] : 0, in ? ub[q0 + lane] : 0);
+}
+
+__device__ inline double readlane_f64(double x, int l) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Cholesky of one 7x7 diagonal block D and the inverse of its factor, by one
+// wavefront: lane i < 7 holds row i (right-looking, a column's entries read from their
+// lanes), then lane c column c of the inverse. One lane alone forms every sum in turn;
+// here a column's run side by side (in the same order, so to the same bits: square
+// root and division per pivot, whose rounding a damped solve near convergence turns
+// into more or fewer trials). The inverse goes to Di, sDi (LDS) and, its lower triangle, to
+// copy[e * cstride] when given: the triangular solves that use the block need no
+// divisions. False (in every lane) if a pivot is not positive.
+__device__ inline bool chol7_wave(const double* D, double* Di, double* sDi, double* copy, int cstride, int lane) {
+  const int r = lane < 7 ? lane : 6;
+  double a[7], rinv[7];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) a[k] = D[7 * r + (k <= r ? k : r)];  // above the diagonal: never read
   bool ok = true;
 #pragma unroll
-  for (int i = 0; i < 7; ++i) {
+  for (int k = 0; k < 7; ++k) {
+    const double x = readlane_f64(a[k], k);
+    ok = ok && x > 0.0;
+    rinv[k] = 1.0 / sqrt(x > 0.0 ? x : 1.0);
+    a[k] *= rinv[k];
 #pragma unroll
-    for (int k = 0; k <= i; ++k) {
-      double v = D[7 * i + k];
-#pragma unroll
-      for (int q = 0; q < k; ++q) v -= L[i][q] * L[k][q];
-      if (k == i) {
-        ok = ok && v > 0.0;
-        L[i][i] = sqrt(v > 0.0 ? v : 1.0);
-        rinv[i] = 1.0 / L[i][i];
-      } else {
-        L[i][k] = v * rinv[k];
-      }
-    }
+    for (int j = k + 1; j < 7; ++j) a[j] -= a[k] * readlane_f64(a[k], j);
   }
+  double t[7];
 #pragma unroll
-  for (int i = 0; i < 7; ++i)
+  for (int i = 0; i < 7; ++i) t[i] = i == lane ? 1.0 : 0.0;
 #pragma unroll
-    for (int k = 0; k < 7; ++k) D[7 * i + k] = k <= i ? L[i][k] : 0.0;
-  // column j of L^{-1} by forward substitution against e_j
+  for (int k = 0; k < 7; ++k) {
+    t[k] *= rinv[k];
 #pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    double v[7];
+    for (int i = k + 1; i < 7; ++i) t[i] -= readlane_f64(a[k], i) * t[k];
+  }
+  if (lane < 7) {
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
-      if (i < j) {
-        v[i] = 0.0;
-      } else if (i == j) {
-        v[i] = rinv[j];
-      } else {
-        double t = 0.0;
-#pragma unroll
-        for (int k = j; k < i; ++k) t += L[i][k] * v[k];
-        v[i] = -t * rinv[i];
-      }
-      Di[7 * i + j] = v[i];
-      if (copy && i >= j) copy[(i * (i + 1) / 2 + j) * cstride] = v[i];
+      sDi[7 * i + lane] = t[i];
+      Di[7 * i + lane] = t[i];
+      if (copy && i >= lane) copy[(i * (i + 1) / 2 + lane) * cstride] = t[i];
     }
   }
   return ok;
@@ -481,7 +488,7 @@ __global__ __launch_bounds__(PGO_WG) void k_pgo_chi2(PgoDev d, int it) {
 //  k_pgo_level_updates: every target of the level's columns (a diagonal block or
 //    an off-diagonal block that receives updates) takes its updates L_a L_b^T from
 //    the factored columns below, one wavefront per target across the chip;
-//  k_pgo_level_factor: a workgroup per column; one lane factors and inverts the
+//  k_pgo_level_factor: a workgroup per column; one wavefront factors and inverts the
 //    diagonal block, and one thread per row forms the off-diagonal rows
 //    L_ij = S_ij L_jj^{-T}.
 constexpr int LEV_WG = 256;
@@ -512,7 +519,10 @@ __global__ __launch_bounds__(LEV_WG) void k_pgo_level_factor(PgoDev d, int l, Le
     // coalesced read per element for a level's columns and blocks)
     const int pj = j - la.j0, NJ = la.NJ;
     double* bwc = d.bw ? d.bw + la.dc + pj : nullptr;
-    if (threadIdx.x == 0) s_fail = chol7_lane(d.Ld + 49 * col, sDi, bwc, NJ) ? 0 : 1;
+    if (wv == 0) {
+      const bool ok = chol7_wave(d.Ld + 49 * col, d.Di + 49 * col, sDi, bwc, NJ, lane);
+      if (lane == 0) s_fail = ok ? 0 : 1;
+    }
     // forward solve of this column, y_c = L_cc^{-1} (y_c - sum_k L_ck y_k): its row blocks
     // (c, k) lie in factored columns of lower levels, whose y_k are final; per-thread
     // sums over the blocks (strided), then a fixed tree
@@ -538,7 +548,6 @@ __global__ __launch_bounds__(LEV_WG) void k_pgo_level_factor(PgoDev d, int l, Le
       if (threadIdx.x == 0) *d.status = 2;
       return;
     }
-    if (threadIdx.x >= 64 && threadIdx.x < 64 + 49) d.Di[49 * col + threadIdx.x - 64] = sDi[threadIdx.x - 64];
     if (threadIdx.x == 0) {
       double v[7];
 #pragma unroll
@@ -563,6 +572,141 @@ __global__ __launch_bounds__(LEV_WG) void k_pgo_level_factor(PgoDev d, int l, Le
       trsm_row(d.Lb + 49 * (b0 + x / 7) + 7 * (x % 7), sDi,
                d.bw ? d.bw + la.lb + 7 * (x % 7) * NQ + pq + x / 7 : nullptr, NQ);
     __syncthreads();
+  }
+}
+
+// Consecutive levels of few columns and targets, by one workgroup in one launch: a
+// wavefront per target, a barrier, a wavefront per column, a barrier. Two launches a
+// level take 10 us whatever they compute; here a level is its own chain of loads. The
+// index lists, which do not depend on the values, come in ahead: the levels'
+// columns and targets into LDS at the start, a level's block lists while the level before
+// it is worked on. 10 steps of 52 nodes with 6 loops (18 levels) 2809 -> 1885 us, of 1,000
+// nodes with 30 loops (105 levels) 15.7 -> 12.1 ms. The line is a column and two targets a
+// wavefront: without the lists ahead those 1,000 nodes took 13.0 ms with it, 13.6 with
+// twice as many, 15.7 with four times (15.6 with two launches a level).
+constexpr int RUN_WG = 512, RUN_WAVES = RUN_WG / 64;
+constexpr int RUN_COLS = RUN_WAVES, RUN_TGTS = 2 * RUN_WAVES;
+constexpr int RUN_MAX = 64;  // levels of one launch
+struct RunCol {
+  int32_t col, f0, f1, b0, nb, pq;  // column, its forward-solve list, first block, blocks, place in the copy
+};
+struct RunTgt {
+  int32_t tgt, q0, q1;  // target, its update list
+};
+__global__ __launch_bounds__(RUN_WG) void k_pgo_level_run(PgoDev d, int l0, int n) {
+  __shared__ int lv[RUN_MAX + 1][LVW + 2];
+  __shared__ RunCol cols[RUN_MAX + 1][RUN_COLS];
+  __shared__ RunTgt tgts[RUN_MAX + 1][RUN_TGTS];
+  __shared__ double sD[RUN_WAVES][49];
+  __shared__ int s_fail;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid < n) {
+    const int* e = d.lv + LVW * (l0 + tid);
+    for (int u = 0; u < LVW; ++u) lv[tid][u] = e[u];
+    lv[tid][LVW] = d.ct_ptr[e[0]];
+    lv[tid][LVW + 1] = d.ct_ptr[e[1]];
+  }
+  if (tid == 0) s_fail = 0;
+  __syncthreads();
+  // entries past a level's columns and targets, and the level past the last: empty lists
+  for (int x = tid; x < (n + 1) * RUN_COLS; x += RUN_WG) {
+    const int l = x / RUN_COLS, j = l < n ? lv[l][0] + x % RUN_COLS : 0;
+    RunCol c{-1, 0, 0, 0, 0, 0};
+    if (l < n && j < lv[l][1]) {
+      c.col = d.flev_col[j];
+      c.f0 = d.fs_ptr[j];
+      c.f1 = d.fs_ptr[j + 1];
+      c.b0 = d.col_ptr[c.col];
+      c.nb = d.col_ptr[c.col + 1] - c.b0;
+      c.pq = d.bs_ptr[j] - lv[l][2];
+    }
+    cols[l][x % RUN_COLS] = c;
+  }
+  for (int x = tid; x < (n + 1) * RUN_TGTS; x += RUN_WG) {
+    const int l = x / RUN_TGTS, i = l < n ? lv[l][LVW] + x % RUN_TGTS : 0;
+    RunTgt t{-1, 0, 0};
+    if (l < n && i < lv[l][LVW + 1]) t = RunTgt{d.lt_tgt[i], d.fu_ptr[i], d.fu_ptr[i + 1]};
+    tgts[l][x % RUN_TGTS] = t;
+  }
+  __syncthreads();
+  double* sDi = sD[wv];
+  // the lane's entries of its wavefront's lists: the targets' first 64 updates, the
+  // column's first 64 forward-solve blocks and their columns
+  int ia[2], ib[2], fb, fc;
+  auto lists = [&](int l, int (&a)[2], int (&b)[2], int& f) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const RunTgt t = tgts[l][wv + u * RUN_WAVES];
+      const bool in = t.q0 + lane < t.q1;
+      a[u] = in ? d.fu_a[t.q0 + lane] : 0;
+      b[u] = in ? d.fu_b[t.q0 + lane] : 0;
+    }
+    const RunCol c = cols[l][wv];
+    f = c.f0 + lane < c.f1 ? d.fs_blk[c.f0 + lane] : -1;
+  };
+  lists(0, ia, ib, fb);
+  fc = fb >= 0 ? d.blk_col[fb] : 0;
+  for (int l = 0; l < n; ++l) {
+    int na[2], nb2[2], nf;
+    lists(l + 1, na, nb2, nf);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const RunTgt t = tgts[l][wv + u * RUN_WAVES];
+      if (t.tgt < 0) continue;
+      double* e = target_elem(d, t.tgt, lane);
+      update_target(d, e, e, t.q0, t.q1, d.fu_a, d.fu_b, lane, ia[u], ib[u]);
+    }
+    const int nc = nf >= 0 ? d.blk_col[nf] : 0;
+    __syncthreads();
+    const RunCol c = cols[l][wv];
+    if (c.col >= 0) {
+      const int NQ = lv[l][6], NJ = lv[l][7];
+      double* bwc = d.bw ? d.bw + lv[l][5] + wv : nullptr;
+      double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+      for (int q = c.f0 + lane; q < c.f1; q += 64) {
+        const int b = q == c.f0 + lane ? fb : d.fs_blk[q];
+        const double* L = d.Lb + 49 * b;
+        const double* y = d.g + 7 * (q == c.f0 + lane ? fc : d.blk_col[b]);
+        double yv[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) yv[u] = y[u];
+#pragma unroll
+        for (int r = 0; r < 7; ++r)
+#pragma unroll
+          for (int u = 0; u < 7; ++u) acc[r] += L[7 * r + u] * yv[u];
+      }
+      if (chol7_wave(d.Ld + 49 * c.col, d.Di + 49 * c.col, sDi, bwc, NJ, lane)) {
+        wave_totals_f64(acc);
+        wave_sync();
+        if (lane < 7) {  // y_c = L_cc^{-1} (y_c - sum), a row per lane (zeros above the diagonal)
+          double v[7], t = 0.0;
+#pragma unroll
+          for (int k = 0; k < 7; ++k) v[k] = d.g[7 * c.col + k] - acc[k];
+#pragma unroll
+          for (int k = 0; k < 7; ++k) t = fma(sDi[7 * lane + k], v[k], t);
+          wave_sync();
+          d.g[7 * c.col + lane] = t;
+          if (bwc) bwc[(28 + lane) * NJ] = t;
+        }
+        for (int r = lane; r < 7 * c.nb; r += 64)
+          trsm_row(d.Lb + 49 * (c.b0 + r / 7) + 7 * (r % 7), sDi,
+                   d.bw ? d.bw + lv[l][4] + 7 * (r % 7) * NQ + c.pq + r / 7 : nullptr, NQ);
+      } else if (lane == 0) {
+        s_fail = 1;
+      }
+    }
+    __syncthreads();
+    if (s_fail) {
+      if (tid == 0) *d.status = 2;
+      return;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      ia[u] = na[u];
+      ib[u] = nb2[u];
+    }
+    fb = nf;
+    fc = nc;
   }
 }
 
@@ -647,13 +791,6 @@ __global__ __launch_bounds__(256) void k_pgo_front_init(PgoDev d) {
   if (x >= n * n) return;
   const size_t r = x % n, c = x / n;
   d.F[x] = (r == c && r >= (size_t)(7 * d.K)) ? 1.0 : 0.0;
-}
-
-__device__ inline double readlane_f64(double x, int l) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 // LDS of the diagonal-block factor: columns being broadcast (two buffers used in turn).
@@ -1662,6 +1799,15 @@ int fail(int* last_hip, hipError_t e) {
 
 namespace {
 
+// The end of the run of levels from l that one workgroup takes (k_pgo_level_run).
+int level_run_end(const std::vector<int32_t>& flev, const std::vector<int32_t>& ct, int l) {
+  const int l0 = l;
+  while (l + 1 < (int)flev.size() && l - l0 < RUN_MAX && flev[l + 1] - flev[l] <= RUN_COLS &&
+         ct[flev[l + 1]] - ct[flev[l]] <= RUN_TGTS)
+    ++l;
+  return l;
+}
+
 // One damped solve and update of the poses (or, without update, only chi^2 at the
 // current linearisation): assembly across the chip, the sparse factorisation and
 // forward solve level by level across the chip, the front's sparse-column updates
@@ -1676,6 +1822,12 @@ hipError_t launch_iteration(const PgoDev& d, const std::vector<int32_t>& flev, c
   const int ga = (int)std::min<int64_t>((work + 255) / 256, 4096);
   hipLaunchKernelGGL(k_pgo_assemble, dim3(ga), dim3(256), 0, st, d, lambda, lm);
   for (int l = 0; l + 1 < (int)flev.size(); ++l) {
+    const int end = level_run_end(flev, ct, l);
+    if (end > l + 1) {
+      hipLaunchKernelGGL(k_pgo_level_run, dim3(1), dim3(RUN_WG), 0, st, d, l, end - l);
+      l = end - 1;
+      continue;
+    }
     const int ntgt = ct[flev[l + 1]] - ct[flev[l]], ncol = flev[l + 1] - flev[l];
     if (ntgt > 0) {
       const int g = std::min((ntgt + LEV_WG / 64 - 1) / (LEV_WG / 64), 1024);
