@@ -114,7 +114,7 @@ struct PgoDev {
   double* M;      // [E][49] per-edge psi A^T Omega A
   double* Aw;     // [E][56] per-edge Jacobian A and Om e (scratch of the linearisation)
   double* v;      // [E][7]  per-edge psi A^T Omega e
-  double* r2;     // [E]     e^T Omega e
+  double* r2;     // [E + 2] e^T Omega e; the predicted reduction and the status of the solve before
   double* chi2;   // [iters + 1]
   int32_t* status;
   // Levenberg-Marquardt: the undamped system of the last solve and its predicted reduction
@@ -181,6 +181,10 @@ __global__ __launch_bounds__(64) void k_pgo_linearize(PgoDev d, const s3a_sim3* 
   double q = 0.0;
   for (int a = 0; a < 7; ++a) q += e[a] * Oe[a];
   if (i == 0) d.r2[k] = q;
+  if (i == 0 && k == 0) {  // behind the edges' values: the solve before's prediction and status (one read for a damped trial)
+    d.r2[d.n_edges] = *d.pred;
+    d.r2[d.n_edges + 1] = (double)*d.status;
+  }
   if (r2_only) return;
   double* Ag = d.Aw + 56 * k;
   if (i == 0)
@@ -446,9 +450,16 @@ __device__ inline void trsm_row(double* row, const double* Dinv, double* copy, i
 }
 
 // Assembly of the normal equations from the per-edge linearisations:
-// independent sums, spread over the whole chip.
-__global__ __launch_bounds__(256) void k_pgo_assemble(PgoDev d, double lambda, int lm) {
+// independent sums, spread over the whole chip. For a damped trial (lm) it also keeps
+// the poses in T_bak and clears the status.
+__global__ __launch_bounds__(256) void k_pgo_assemble(PgoDev d, double lambda, int lm, const s3a_sim3* T, s3a_sim3* T_bak) {
   const int gt = blockIdx.x * blockDim.x + threadIdx.x, gs = gridDim.x * blockDim.x;
+  if (lm) {
+    constexpr int W = sizeof(s3a_sim3) / sizeof(double);
+    for (int x = gt; x < d.n_nodes * W; x += gs)
+      reinterpret_cast<double*>(T_bak)[x] = reinterpret_cast<const double*>(T)[x];
+    if (gt == 0) *d.status = 0;
+  }
   // ---- assembly (diagonal blocks, off-diagonal blocks, gradient)
   for (int x = gt; x < d.m * 49; x += gs) {
     const int c = x / 49, a = x % 49;
@@ -1497,6 +1508,7 @@ struct PgoWorkspace {
   double* v_alt = nullptr;
   double* r2_alt = nullptr;
   s3a_sim3* T_bak = nullptr;
+  double* host = nullptr;  // pinned, [n_edges + 2]: what a trial reads back
 };
 
 namespace {
@@ -1815,12 +1827,12 @@ int level_run_end(const std::vector<int32_t>& flev, const std::vector<int32_t>& 
 // per launch, then the backward solves and the update in one workgroup.
 hipError_t launch_iteration(const PgoDev& d, const std::vector<int32_t>& flev, const std::vector<int32_t>& ct,
                             const std::vector<int32_t>& lvh,
-                            s3a_sim3* T, double lambda, int it, int update, int lm, hipStream_t st) {
-  hipLaunchKernelGGL(k_pgo_chi2, dim3(1), dim3(PGO_WG), 0, st, d, it);
+                            s3a_sim3* T, double lambda, int it, int update, int lm, s3a_sim3* T_bak, hipStream_t st) {
+  if (!lm) hipLaunchKernelGGL(k_pgo_chi2, dim3(1), dim3(PGO_WG), 0, st, d, it);
   if (!update || d.m == 0) return hipGetLastError();
   const int64_t work = std::max<int64_t>((int64_t)d.nblk * 49, (int64_t)d.m * 49);
   const int ga = (int)std::min<int64_t>((work + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pgo_assemble, dim3(ga), dim3(256), 0, st, d, lambda, lm);
+  hipLaunchKernelGGL(k_pgo_assemble, dim3(ga), dim3(256), 0, st, d, lambda, lm, T, T_bak);
   for (int l = 0; l + 1 < (int)flev.size(); ++l) {
     const int end = level_run_end(flev, ct, l);
     if (end > l + 1) {
@@ -1859,9 +1871,13 @@ double huber_energy(const std::vector<double>& r2, double delta) {
 }
 
 // Levenberg-Marquardt driver: every trial is one damped solve on the device
-// (launch_iteration, which also leaves the predicted reduction), a
-// linearisation at the trial poses into the second buffer set, and a read of
-// the trial's per-edge e^T Omega e to decide on the host.
+// (launch_iteration, which also keeps the poses before it and leaves the predicted
+// reduction), a linearisation at the trial poses into the second buffer set, and one
+// read, of the trial's per-edge e^T Omega e with the prediction and the status behind
+// them, to decide on the host. (The linearisation is wasted on a trial that failed or
+// had nothing left to gain; a read of its own for those two cost every trial a
+// synchronisation and two copies: a solve of 52 nodes 1973 -> 1468 us together with the
+// backup in the assembly.)
 int pgo_solve_lm(PgoWorkspace* ws, int* last_hip, int32_t n_nodes, int32_t n_edges, const s3a_sim3* T_meas,
                  const double* omega, s3a_sim3* T, const s3a_pgo_params& p, s3a_pgo_report* report, hipStream_t st) {
   PgoDev cur = ws->dev, trial = ws->dev;
@@ -1872,11 +1888,13 @@ int pgo_solve_lm(PgoWorkspace* ws, int* last_hip, int32_t n_nodes, int32_t n_edg
   double lam = p.lambda > 0.0 ? p.lambda : 1e-4, nu = 2.0;
   std::vector<double> r2(n_edges), r2t(n_edges), chi;
   hipError_t e = hipSuccess;
+  const double* tail = ws->host + n_edges;  // the prediction and the status
   auto linearize = [&](const PgoDev& dd, std::vector<double>& out) -> hipError_t {
     if (n_edges == 0) return hipSuccess;
     hipError_t ee = launch_linearize(dd, T_meas, omega, T, p.huber_delta, 0, st);
-    if (ee == hipSuccess) ee = hipMemcpyAsync(out.data(), dd.r2, sizeof(double) * n_edges, hipMemcpyDeviceToHost, st);
+    if (ee == hipSuccess) ee = hipMemcpyAsync(ws->host, dd.r2, sizeof(double) * (n_edges + 2), hipMemcpyDeviceToHost, st);
     if (ee == hipSuccess) ee = hipStreamSynchronize(st);
+    if (ee == hipSuccess) std::copy(ws->host, ws->host + n_edges, out.begin());
     return ee;
   };
   auto sum = [](const std::vector<double>& x) {
@@ -1891,16 +1909,10 @@ int pgo_solve_lm(PgoWorkspace* ws, int* last_hip, int32_t n_nodes, int32_t n_edg
   for (int it = 0; it < p.iters && cur.m > 0 && n_edges > 0; ++it) {
     bool kept = false;
     for (int rej = 0; rej < max_rej; ++rej) {
-      e = hipMemcpyAsync(ws->T_bak, T, sizeof(s3a_sim3) * n_nodes, hipMemcpyDeviceToDevice, st);
-      if (e == hipSuccess) e = launch_fill_zero(reinterpret_cast<uint32_t*>(cur.status), 1, st);
-      if (e != hipSuccess) return fail(last_hip, e);
-      if ((e = launch_iteration(cur, ws->flev, ws->ct, ws->lvh, T, lam, it, 1, 1, st)) != hipSuccess) return fail(last_hip, e);
-      int32_t fst = 0;
-      double pred = 0.0;
-      e = hipMemcpyAsync(&fst, cur.status, sizeof(int32_t), hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(&pred, cur.pred, sizeof(double), hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-      if (e != hipSuccess) return fail(last_hip, e);
+      if ((e = launch_iteration(cur, ws->flev, ws->ct, ws->lvh, T, lam, it, 1, 1, ws->T_bak, st)) != hipSuccess) return fail(last_hip, e);
+      if ((e = linearize(trial, r2t)) != hipSuccess) return fail(last_hip, e);
+      const double pred = tail[0];
+      const int32_t fst = (int32_t)tail[1];
       status = fst;
       if (fst == 0 && pred <= 1e-15 * F) {  // below what F resolves: converged
         e = hipMemcpyAsync(T, ws->T_bak, sizeof(s3a_sim3) * n_nodes, hipMemcpyDeviceToDevice, st);
@@ -1909,7 +1921,6 @@ int pgo_solve_lm(PgoWorkspace* ws, int* last_hip, int32_t n_nodes, int32_t n_edg
         break;
       }
       if (fst == 0) {
-        if ((e = linearize(trial, r2t)) != hipSuccess) return fail(last_hip, e);
         const double Ft = huber_energy(r2t, p.huber_delta);
         if (pred > 0.0 && Ft < F) {
           const double rho = (F - Ft) / pred;
@@ -2041,6 +2052,7 @@ hipError_t launch_edges_from_alignment(int n, const s3a_sim3* S, const s3a_align
 void pgo_free(PgoWorkspace* ws) {
   if (!ws) return;
   if (ws->buf) (void)hipFree(ws->buf);
+  if (ws->host) (void)hipHostFree(ws->host);
   delete ws;
 }
 
@@ -2091,10 +2103,10 @@ int pgo_solve(PgoWorkspace** wsp, int* last_hip, int32_t n_nodes, int32_t n_edge
              bytes_of<int32_t>(S.lv.size() + LVW) + bytes_of<double>((size_t)S.bw_size + 1);
     total += bytes_of<int32_t>(S.chain.size() + 4) + bytes_of<int32_t>(S.chain_lev.size());
     total += bytes_of<double>(49 * (size_t)m) * 2 + bytes_of<double>(49 * (size_t)nb + 49) + bytes_of<double>(7 * (size_t)m + 7);
-    total += bytes_of<double>(49 * (size_t)E + 49) + bytes_of<double>(7 * (size_t)E + 7) + bytes_of<double>(E + 1);
+    total += bytes_of<double>(49 * (size_t)E + 49) + bytes_of<double>(7 * (size_t)E + 7) + bytes_of<double>(E + 2);
     total += bytes_of<double>(iters_cap) + bytes_of<int32_t>(4);
     total += bytes_of<double>(7 * (size_t)m + 7) * 2 + bytes_of<double>(8);  // LM: gsave, dsave, pred
-    total += bytes_of<double>(49 * (size_t)E + 49) + bytes_of<double>(7 * (size_t)E + 7) + bytes_of<double>(E + 1);
+    total += bytes_of<double>(49 * (size_t)E + 49) + bytes_of<double>(7 * (size_t)E + 7) + bytes_of<double>(E + 2);
     total += bytes_of<s3a_sim3>(n_nodes);
     total += bytes_of<double>(56 * (size_t)E + 56);  // Aw
     total += bytes_of<double>((size_t)S.nF * S.nF + 1) + bytes_of<double>((size_t)S.nF * FB + 1) +
@@ -2105,9 +2117,19 @@ int pgo_solve(PgoWorkspace** wsp, int* last_hip, int32_t n_nodes, int32_t n_edge
       (void)hipFree(ws->buf);
       ws->buf = nullptr;
     }
+    if (ws->host) {
+      (void)hipHostFree(ws->host);
+      ws->host = nullptr;
+    }
     void* buf = nullptr;
     hipError_t e = hipMalloc(&buf, total);
     if (e != hipSuccess) return fail(last_hip, e);
+    e = hipHostMalloc(reinterpret_cast<void**>(&ws->host), sizeof(double) * ((size_t)E + 2), hipHostMallocDefault);
+    if (e != hipSuccess) {
+      (void)hipFree(buf);
+      ws->host = nullptr;
+      return fail(last_hip, e);
+    }
     ws->buf = buf;
     char* c = static_cast<char*>(buf);
     PgoDev& d = ws->dev;
@@ -2171,7 +2193,7 @@ int pgo_solve(PgoWorkspace** wsp, int* last_hip, int32_t n_nodes, int32_t n_edge
     d.M = carve<double>(c, 49 * (size_t)E + 49);
     d.Aw = carve<double>(c, 56 * (size_t)E + 56);
     d.v = carve<double>(c, 7 * (size_t)E + 7);
-    d.r2 = carve<double>(c, E + 1);
+    d.r2 = carve<double>(c, E + 2);
     d.chi2 = carve<double>(c, iters_cap);
     d.status = carve<int32_t>(c, 4);
     d.gsave = carve<double>(c, 7 * (size_t)m + 7);
@@ -2179,7 +2201,7 @@ int pgo_solve(PgoWorkspace** wsp, int* last_hip, int32_t n_nodes, int32_t n_edge
     d.pred = carve<double>(c, 8);
     ws->M_alt = carve<double>(c, 49 * (size_t)E + 49);
     ws->v_alt = carve<double>(c, 7 * (size_t)E + 7);
-    ws->r2_alt = carve<double>(c, E + 1);
+    ws->r2_alt = carve<double>(c, E + 2);
     ws->T_bak = carve<s3a_sim3>(c, n_nodes);
     d.F = carve<double>(c, (size_t)S.nF * S.nF + 1);
     d.Finv = carve<double>(c, (size_t)S.nF * FB + 1);
@@ -2221,7 +2243,7 @@ int pgo_solve(PgoWorkspace** wsp, int* last_hip, int32_t n_nodes, int32_t n_edge
       if ((e = launch_linearize(d, T_meas, omega, T, p.huber_delta, !update, st)) != hipSuccess) return fail(last_hip, e);
     }
     if (update && d.m == 0) continue;
-    if ((e = launch_iteration(d, ws->flev, ws->ct, ws->lvh, T, p.lambda, it, update, 0, st)) != hipSuccess) return fail(last_hip, e);
+    if ((e = launch_iteration(d, ws->flev, ws->ct, ws->lvh, T, p.lambda, it, update, 0, nullptr, st)) != hipSuccess) return fail(last_hip, e);
   }
   if (report) {
     std::vector<double> chi(p.iters + 1, 0.0);
