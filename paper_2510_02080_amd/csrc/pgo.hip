@@ -825,55 +825,73 @@ __shared__ double front_cb[2 * (FB + 1)];
 constexpr int FRONT_TWG = 256;
 
 // (1) on the chain: the FB x FB diagonal block at (kd, kd) factored by one
-// wavefront (lane = row, right-looking: the pivot is read from its lane, each
-// updated column goes to LDS one step before it is needed) from src (element
-// (i, c) at src[c * ld + i]: the block in F, or a copy in LDS) into F; 1 / L_jj
-// to rd. False (in every lane) if a pivot is not positive.
+// wavefront, right-looking: lane i holds the even columns of row i, lane i + 32 the odd
+// ones (half the updates, LDS reads and registers of a whole row per lane). Step k: the
+// updated column k is in LDS since the step before, its pivot is read from its lane, and
+// column k + 1 goes to LDS before the others are updated. From src (element (i, c) at
+// src[c * ld + i]: the block in F, or a copy in LDS) into F; 1 / L_jj to rd. False (in
+// every lane) if a pivot is not positive. Bound by a step's chain (the column through
+// LDS, then the pivot's); with a row per lane, 32 lanes idle, a panel launch took 15.0 us and
+// the first block's 8.1, with two lanes 14.0 and 6.9.
 __device__ __attribute__((always_inline)) inline bool front_factor(const double* src, int ld, double* F, int n, int kd,
                                                                   int lane, double* rd) {
+  static_assert(FB == 32, "two lanes a row");
+  constexpr int H = FB / 2;
   double* cb = front_cb;
-  const int r = lane < FB ? lane : FB - 1, e = lane < FB ? lane : FB;
-  double a[FB];  // row r; entries above the diagonal carry values that are never read
+  const int r = lane & 31, odd = lane >> 5;
+  double a[H];  // columns 2 u + odd of row r; entries above the diagonal carry values that are never read
 #pragma unroll
-  for (int c = 0; c < FB; ++c) a[c] = src[(size_t)c * ld + (c <= r ? r : c)];
+  for (int u = 0; u < H; ++u) {
+    const int c = 2 * u + odd;
+    a[u] = src[(size_t)c * ld + (c <= r ? r : c)];
+  }
   bool ok = true;
   double rv = 1.0;
-  cb[e] = a[0];
+  if (!odd) cb[r] = a[0];
   wave_sync();
 #pragma unroll
   for (int k = 0; k < FB; ++k) {
     double* cur = cb + (k & 1) * (FB + 1);
     double* nxt = cb + ((k + 1) & 1) * (FB + 1);
-    // the column's entries below the pivot, all read before the pivot's chain
-    // (their LDS latency overlaps it instead of each read waiting in turn)
-    double cv[FB];
+    // the row's entry of column k and the column's entries below the pivot that this
+    // lane's columns need, all read before the pivot's chain (their LDS latency overlaps it
+    // instead of each read waiting in turn)
+    const double own = cur[r];
+    double cv[H];
 #pragma unroll
-    for (int j = k + 1; j < FB; ++j) cv[j] = cur[j];
+    for (int u = (k + 1) / 2; u < H; ++u) cv[u] = cur[2 * u + odd];
     __builtin_amdgcn_sched_barrier(0);
-    const double dkk = readlane_f64(a[k], k);
+    const double dkk = readlane_f64(a[k / 2], k + 32 * (k & 1));
     ok = ok && dkk > 0.0;
     const double x = dkk > 0.0 ? dkk : 1.0;
     double rk = __builtin_amdgcn_rsq(x);
     rk = rk * fma(-0.5 * x * rk, rk, 1.5);
     rk = rk * fma(-0.5 * x * rk, rk, 1.5);
-    const double lkk = x * rk;
-    a[k] = lane == k ? lkk : a[k] * rk;
-    rv = lane == k ? rk : rv;
-    const double m = a[k] * rk;  // L_rk / L_kk, and L_jk = cur[j] / L_kk
+    const double lk = r == k ? x * rk : own * rk;
+    if (odd == (k & 1)) a[k / 2] = lk;
+    rv = r == k ? rk : rv;
+    const double m = lk * rk;  // L_rk / L_kk, and L_jk = cur[j] / L_kk
     if (k + 1 < FB) {
-      a[k + 1] -= m * cv[k + 1];
-      nxt[e] = a[k + 1];
+      const int u1 = (k + 1) / 2;
+      if (odd == ((k + 1) & 1)) {
+        a[u1] -= m * cv[u1];
+        nxt[r] = a[u1];
+      }
     }
 #pragma unroll
-    for (int j = k + 2; j < FB; ++j) a[j] -= m * cv[j];
+    for (int u = (k + 1) / 2; u < H; ++u) {
+      if (u == (k + 1) / 2) {  // column k + 1 is done; its pair, where it comes later, is not
+        if ((k + 1) % 2 == 0 && odd) a[u] -= m * cv[u];
+      } else {
+        a[u] -= m * cv[u];
+      }
+    }
     wave_sync();
   }
-  if (lane < FB) {
 #pragma unroll
-    for (int c = 0; c < FB; ++c)
-      if (c <= lane) F[(size_t)(kd + c) * n + kd + lane] = a[c];
-    rd[lane] = rv;
-  }
+  for (int u = 0; u < H; ++u)
+    if (2 * u + odd <= r) F[(size_t)(kd + 2 * u + odd) * n + kd + r] = a[u];
+  if (!odd) rd[r] = rv;
   return ok;
 }
 
