@@ -7,8 +7,8 @@ storage. Only pairs whose pose matches the FP64 oracle within 1e-5 rad
 (rotation) and 1e-5 relative (scale, translation) count.
 
 One timed step = one s3a_align_pairs call over the whole batch (inputs
-resident in HBM; a captured graph of one streaming launch and one FP64
-finalize launch per pass, replayed).
+resident in HBM; one schedule launch, then one streaming launch and one
+FP64 finalize launch per pass).
 Other legs on the same line, each with its own timing: the same batch in
 BF16 storage, the same batch as one persistent launch, the plain per-pair
 path (one pair at a time, one launch per pass), depth-map input, point
@@ -233,7 +233,7 @@ def main():
                     oracle_cpu_s=float(sum(o[4] for o in out)), wall_s=wall,
                     oracle_points=int(sum(o[3] for o in out)))
 
-    # ---- headline: batched FP32, graph of per-pass launches
+    # ---- headline: batched FP32, a launch per pass
     pm = s3a.Pointmaps.from_batch(b2, dev)
     tune = None
     if args.tuning:
@@ -264,8 +264,8 @@ def main():
     res["batched_fp32"] = dict(ms_per_step=ms, kernel_ms=k_ms, points_per_s=value, verify=ver, tuning=tune)
     log(f"verify fp32: {ver}")
 
-    # ---- the same batch as one persistent launch (pass-major tickets), graph-captured, with its
-    # own autotuned shape (workgroups per CU instead of one per tile); then back to the graph path's
+    # ---- the same batch as one persistent launch (pass-major tickets), with its own autotuned
+    # shape (workgroups per CU instead of one per tile); then back to the per-pass path's
     if "persistent" in legs:
         retune = not args.no_autotune and not args.tuning
         tune_p = h.autotune(pm, b2.tau, b2.delta, b2.iters, flags=s3a.FLAG_PERSISTENT) if retune else None
@@ -275,17 +275,17 @@ def main():
         kp, _ = kernel_ms(stepp, args.steps)
         Sp, ibp = h.align_pairs(pm, b2.tau, b2.delta, b2.iters, flags=s3a.FLAG_PERSISTENT)
         torch.cuda.synchronize()
-        if retune:  # the handle keeps one tuned shape per size: the graph path's again
+        if retune:  # the handle keeps one tuned shape per size: the per-pass path's again
             h.autotune(pm, b2.tau, b2.delta, b2.iters)
         # bit for bit equal only when both paths use the same tile size
         same = bool(torch.equal(Sp, S)) and bool(torch.equal(ibp, ib))
-        # bitwise equal to the checked graph-path result: the oracle verdict carries over
+        # bitwise equal to the checked per-pass result: the oracle verdict carries over
         verp = dict(ver, bitwise_equal_to="batched_fp32") if (same and ver is not None) else verify("cfg2", Sp, ibp)
         res["persistent_fp32"] = dict(ms_per_step=ms_p, kernel_ms=kp,
                                       points_per_s=counted_points(verp, V_total) / (ms_p / 1e3),
                                       vs_graph_path=ms / ms_p, bitwise_equal_graph_path=same, tuning=tune_p,
                                       verify=verp)
-        log(f"persistent fp32: {ms_p:.3f} ms/step (kernel {kp:.3f} ms, shape {tune_p}), graph path {ms:.3f} ms, "
+        log(f"persistent fp32: {ms_p:.3f} ms/step (kernel {kp:.3f} ms, shape {tune_p}), per-pass launches {ms:.3f} ms, "
             f"bitwise equal {same}")
 
     # ---- BF16 storage
@@ -534,7 +534,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "batched: 256 pairs, valid counts log-uniform 20k-400k (518x392 / 518x518 frames), "
-                               "FP32 SoA storage, Umeyama + 10 Huber IRLS steps, one graph of 11 pass launches",
+                               "FP32 SoA storage, Umeyama + 10 Huber IRLS steps, 11 pass launches",
                    "n_pairs": b2.n_pairs, "n_points": b2.n_points, "irls_iters": b2.iters,
                    "huber_delta": b2.delta, "conf_threshold": b2.tau},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
