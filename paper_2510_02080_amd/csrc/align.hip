@@ -53,8 +53,19 @@ __device__ inline bool depth_prep(const s3a_depth_pair& src, int64_t n, DepthPai
   return ok;
 }
 
+// A camera without NaN or infinities, in pass form too (a focal length of zero).
+__device__ inline bool camera_finite(const s3a_camera& c) {
+  float z = fmaf(1.0f / c.fx, 0.0f, fmaf(c.cx / c.fx, 0.0f, fmaf(1.0f / c.fy, 0.0f, c.cy / c.fy * 0.0f)));  // stays zero
+  for (int i = 0; i < 9; ++i) z = fmaf(c.R[i], 0.0f, z);
+  for (int i = 0; i < 3; ++i) z = fmaf(c.t[i], 0.0f, z);
+  return z == 0.0f;
+}
+
 // Tile j of a pair's range [a, b); depth: the pair's frames, or null. Frames narrower
-// than a vector count as spanned (their pixels go one at a time: see DepthWalk).
+// than a vector count as spanned (their pixels go one at a time: see DepthWalk), and so
+// do frames that are lost, a camera of theirs not finite: the walk of a frame fills in a
+// finite depth where a pixel is masked, which such a camera takes to NaN, while the
+// spanning walk masks the points themselves.
 __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, int ntiles, int j, int64_t T,
                                      const s3a_depth_pair* depth) {
   const int64_t b0 = a & ~(TILE_ALIGN - 1);
@@ -70,7 +81,9 @@ __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, 
     if (depth && depth->width >= 8 && depth->frame_pixels >= depth->width) {
       const int64_t first = t.begin > a ? t.begin : a;
       const int f0 = (int)((first - a) / depth->frame_pixels), f1 = (int)((t.end - 1 - a) / depth->frame_pixels);
-      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first) t.frame = f0;
+      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first && camera_finite(depth->p[f0]) &&
+          camera_finite(depth->q[f0]))
+        t.frame = f0;
     }
   } else {
     t.begin = t.end = t.lo = a;
