@@ -53,19 +53,22 @@ __device__ inline bool depth_prep(const s3a_depth_pair& src, int64_t n, DepthPai
   return ok;
 }
 
-// A camera without NaN or infinities, in pass form too (a focal length of zero).
-__device__ inline bool camera_finite(const s3a_camera& c) {
-  float z = fmaf(1.0f / c.fx, 0.0f, fmaf(c.cx / c.fx, 0.0f, fmaf(1.0f / c.fy, 0.0f, c.cy / c.fy * 0.0f)));  // stays zero
-  for (int i = 0; i < 9; ++i) z = fmaf(c.R[i], 0.0f, z);
-  for (int i = 0; i < 3; ++i) z = fmaf(c.t[i], 0.0f, z);
-  return z == 0.0f;
+// A camera without NaN or infinities (also a focal length of zero), whose rays and
+// centre are such that a depth below EXTREME / PLAIN_RAY gives no extreme point, and one
+// below 1e30 a finite one.
+__device__ inline bool camera_plain(const s3a_camera& c, int width, int rows) {
+  float G = 0.0f, t = 0.0f;
+  for (int i = 0; i < 9; ++i) G += fabsf(c.R[i]);
+  for (int i = 0; i < 3; ++i) t += fabsf(c.t[i]);
+  const float ray = fabsf(1.0f / c.fx) * (float)width + fabsf(c.cx / c.fx) + fabsf(1.0f / c.fy) * (float)rows + fabsf(c.cy / c.fy);
+  return G * (ray + 1.0f) < PLAIN_RAY && t < EXTREME;  // (false for a NaN)
 }
 
 // Tile j of a pair's range [a, b); depth: the pair's frames, or null. Frames narrower
 // than a vector count as spanned (their pixels go one at a time: see DepthWalk), and so
-// do frames that are lost, a camera of theirs not finite: the walk of a frame fills in a
-// finite depth where a pixel is masked, which such a camera takes to NaN, while the
-// spanning walk masks the points themselves.
+// do frames whose camera is lost or out of all scale: the walk of a frame masks a pixel by
+// its depths, which such a camera takes to NaN all the same, while the spanning walk
+// masks the points themselves.
 __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, int ntiles, int j, int64_t T,
                                      const s3a_depth_pair* depth) {
   const int64_t b0 = a & ~(TILE_ALIGN - 1);
@@ -81,8 +84,8 @@ __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, 
     if (depth && depth->width >= 8 && depth->frame_pixels >= depth->width) {
       const int64_t first = t.begin > a ? t.begin : a;
       const int f0 = (int)((first - a) / depth->frame_pixels), f1 = (int)((t.end - 1 - a) / depth->frame_pixels);
-      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first && camera_finite(depth->p[f0]) &&
-          camera_finite(depth->q[f0]))
+      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first && camera_plain(depth->p[f0], depth->width, depth->frame_pixels / depth->width) &&
+          camera_plain(depth->q[f0], depth->width, depth->frame_pixels / depth->width))
         t.frame = f0;
     }
   } else {
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(SCHED_WG) void k_sched_tiles(Shape sh, CallDesc c, 
     s.tile0 = tile0[k];
     s.ntiles = tile0[k + 1] - tile0[k];
     s.bad = any_bad;
-    s.pad = 0;
+    s.extreme = 0;
     if (c.depth && !depth_prep(c.depth[k], s.b - s.a, w.dpairs + k)) s.bad = 1;
     w.sched[k] = s;
   }
@@ -247,7 +250,8 @@ __global__ __launch_bounds__(WG) void k_pass(Shape sh, const CallDesc* __restric
     if constexpr (ONE) tile_begin<DT, WG>(sh, pl, td, first);
     const PointParams P = load_params(w.params + td.pair);
     const SrcCtx<DT> src = make_src<DT>(pl, w, td);
-    tile_body<DT, MODE, WG, ITEMS, ONE>(sh, src, td, P, first, red, w.partials + (int64_t)t * NSTAT);
+    tile_body<DT, MODE, WG, ITEMS, ONE>(sh, src, td, P, first, red, w.partials + (int64_t)t * NSTAT,
+                                        &w.sched[td.pair].extreme);
     if constexpr (ONE) return;
   }
 }
@@ -265,12 +269,12 @@ __device__ inline bool solve_pass(const Shape& sh, const CallDesc* __restrict__ 
   const int wv = (int)threadIdx.x >> 6;
   double word = 0.0;
   if (KIND != SOLVE_MOMENTS && wv == 0) word = state_word(w.state + (size_t)((done + 1) & 1) * w.pairs_cap + k);
-  const int bad = KIND != SOLVE_GN ? w.sched[k].bad : 0;
+  const int bad = KIND != SOLVE_GN ? w.sched[k].bad : 0, extreme = KIND != SOLVE_GN ? w.sched[k].extreme : 0;
   gather_groups(w.partials + ((size_t)(done & 1) * w.tiles_cap + tile0) * NSTAT, ntiles, wv, 4, S.part);
   if (KIND != SOLVE_MOMENTS && wv == 0) set_state_word(&S.st, word);
   __syncthreads();
   if (wv == 0) {
-    solve_wave<KIND>(sh, cd, k, done, bad != 0, first, S);
+    solve_wave<KIND>(sh, cd, k, done, bad != 0, extreme != 0, first, S);
     if (first) set_state_word(w.state + (size_t)(done & 1) * w.pairs_cap + k, state_word(&S.st));
   }
   __syncthreads();
@@ -309,7 +313,7 @@ __global__ __launch_bounds__(WG) void k_pass_solve(Shape sh, const CallDesc* __r
     P.cf[i] = uniform_f32((float)S.st.cq[i]);
   }
   P.active = 1;
-  P.nonfinite = uniform_i32(S.st.nnf > 0 ? 1 : 0);
+  P.mask = uniform_i32(S.st.mask);
   tile_gn<DT, WG, ITEMS, MODE == MODE_GN, true>(sh, src, td, P, first, red,
                                                 w.partials + ((size_t)(pass & 1) * w.tiles_cap + t) * NSTAT);
 }
@@ -336,9 +340,9 @@ __global__ __launch_bounds__(256) void k_finalize(Shape sh, const CallDesc* __re
   if (wv == 0 && pass > 0) set_state_word(&S.st, word);
   __syncthreads();
   if (wv != 0) return;
-  solve_wave<SOLVE_ANY>(sh, cd, k, pass, sc.bad != 0, true, S);
+  solve_wave<SOLVE_ANY>(sh, cd, k, pass, sc.bad != 0, sc.extreme != 0, true, S);
   set_state_word(w.state + k, state_word(&S.st));
-  if (threadIdx.x == 0) publish(w.params + k, S.st.S, S.st.cq, S.more, S.st.nnf > 0 ? 1 : 0);
+  if (threadIdx.x == 0) publish(w.params + k, S.st.S, S.st.cq, S.more, S.st.mask);
 }
 
 // ------------------------------------------------------------------ cost / adjoint prep

@@ -252,6 +252,28 @@ __device__ inline void zero_rest(const Shape& sh, const Work& w, float* const (&
   }
 }
 
+__device__ inline float max3_abs(float x, float y, float z) { return fmaxf(fmaxf(fabsf(x), fabsf(y)), fabsf(z)); }
+
+// Whether a lane of a moments pass has met a point whose largest value `size` (NaN
+// apart) lies in [from, infinity): the bits of such a size, less from's, are the
+// small unsigned numbers, whose least is kept. (Counted by masks instead, the moments of
+// 256 depth pairs took 225 us, and 211 with all coordinates looked at; 186 without.)
+struct ExtremeSeen {
+  float from;
+  uint32_t least = ~0u;
+  __device__ inline void look(bool in, float size) {
+    const uint32_t u = __float_as_uint(size) - __float_as_uint(from);
+    least = min(least, in ? u : ~0u);
+  }
+  // (In the persistent launch the pair's solve is in the same launch: the flag is out
+  // before the workgroup's barrier and arrival.)
+  __device__ inline void mark(int32_t* flag) const {
+    if (least >= __float_as_uint(__builtin_inff()) - __float_as_uint(from)) return;
+    __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();
+  }
+};
+
 __device__ inline bool finite7(const float* x) {
   bool f = true;
 #pragma unroll
@@ -287,7 +309,7 @@ __device__ inline PointParams load_params(const PointParams* p) {
   r.scale = uniform_f32(p->scale);
   r.L = uniform_f32(p->L);
   r.active = uniform_i32(p->active);
-  r.nonfinite = uniform_i32(p->nonfinite);
+  r.mask = uniform_i32(p->mask);
   return r;
 }
 
@@ -869,16 +891,16 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
   const float tau = sh.tau, delta = sh.delta_f;
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
-  const bool check_finite = P.nonfinite != 0;
+  const bool check_finite = P.mask != MASK_NONE;
   auto fetch = [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); };
   DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
   const CamForm fp(A, cp), fq(cq.R, cq);
   auto body = [&](const typename L::Raw& raw, int rel0) {
     float d[3][VEC];
     L::unpack(raw, d);
-    // a pair's first and last vectors, and in pairs that hold any, pixels whose depths
-    // are not finite or not such that their squares are (the closed form failed then),
-    // or whose confidence is not finite: zeroed, so of weight zero and finite
+    // a pair's first and last vectors, and in pairs that hold any, pixels that are not
+    // finite: zeroed, so of weight zero and finite. (A finite depth of 1e30 or more gives
+    // a point that is not, or the pair is MASK_EXTREME and not walked here.)
     if (check_finite || rel0 < lo_rel || rel0 + VEC > end_rel) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
@@ -918,14 +940,22 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
 // over the few points the lane handles in this tile (then pairwise across
 // lanes, FP64 across wavefronts and tiles). Points outside the pair's range,
 // below the confidence threshold, or (in pairs that hold any) with a NaN/Inf
-// value get zero weight and zeroed coordinates.
+// value get zero weight and zeroed coordinates; in pairs that hold extreme values
+// (PairMask), so does every point of weight zero.
 // Elements of a raw vector that lie outside the pair's range [lo_rel, end_rel),
 // or (check_finite) hold a NaN/Inf in any plane, are zeroed in place: zero
 // weight and zero coordinates. Both cases are rare (a pair's first and last
 // vectors; pairs the moments pass found non-finite values in), so the common
-// vector pays one uniform test each.
-template <int DT>
-__device__ inline void mask_raw(RawVec& r, int rel0, int lo_rel, int end_rel, bool check_finite) {
+// vector pays one uniform test each. check_extreme: so are
+// elements of weight zero.
+// APART: that test stands by itself, which takes the walks' registers from 146 to 114
+// or less (BF16, 256 pairs of 32 M points: 80 -> 75 us a pass). A FP32 walk, bound by the
+// loads, is a hundredth faster without the fourth wavefront (133.8 against 134.5 us), so
+// there it lies inside the other; but not in the solving passes, for whose registers
+// that is worse (one pair of 203,056 points: 120 us a call against 116).
+template <int DT, bool APART>
+__device__ inline void mask_raw(RawVec& r, int rel0, int lo_rel, int end_rel, bool check_finite, bool check_extreme,
+                                float tau) {
   constexpr int VEC = Planes<DT>::VEC;
   if (rel0 < lo_rel || rel0 + VEC > end_rel) {
 #pragma unroll
@@ -939,17 +969,31 @@ __device__ inline void mask_raw(RawVec& r, int rel0, int lo_rel, int end_rel, bo
       for (int j = 0; j < 7; ++j) fin = fin && Planes<DT>::elem_finite(r, j, e);
       Planes<DT>::keep_elem(r, e, fin);
     }
+    if (!APART && check_extreme) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const float c = Planes<DT>::elem(r, 6, e);
+        Planes<DT>::keep_elem(r, e, c >= tau && c > 0.0f);
+      }
+    }
+  }
+  if (APART && __builtin_expect(check_extreme, 0)) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const float c = Planes<DT>::elem(r, 6, e);
+      Planes<DT>::keep_elem(r, e, c >= tau && c > 0.0f);
+    }
   }
 }
 
-template <int DT, bool COST>
+template <int DT, bool COST, bool APART>
 __device__ inline void gn_vector(const Shape& sh, const PointParams& P, RawVec& r, int rel0, int lo_rel,
-                                 int end_rel, bool check_finite, float (&a)[NSTAT]) {
+                                 int end_rel, bool check_finite, bool check_extreme, float (&a)[NSTAT]) {
   constexpr int VEC = Planes<DT>::VEC;
   using L = Planes<DT>;
   const float tau = sh.tau, delta = sh.delta_f;
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
-  mask_raw<DT>(r, rel0, lo_rel, end_rel, check_finite);
+  mask_raw<DT, APART>(r, rel0, lo_rel, end_rel, check_finite, check_extreme, tau);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     const float px = L::elem(r, 0, e), py = L::elem(r, 1, e), pz = L::elem(r, 2, e);
@@ -971,7 +1015,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
 #pragma unroll
   for (int j = 0; j < NSTAT; ++j) a[j] = 0.0f;
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
-    if (P.active && pl.frame >= 0) {
+    if (P.active && pl.frame >= 0 && P.mask != MASK_EXTREME) {
       tile_gn_depth_frame<DT, WG, ITEMS, COST, BEGUN>(sh, pl, td, P, first, a);
       block_store_f32<WG>(a, red, out);
       return;
@@ -979,17 +1023,19 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
   }
   if (P.active) {
     const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
-    const bool check_finite = P.nonfinite != 0;
+    const bool check_finite = P.mask != MASK_NONE, check_extreme = P.mask == MASK_EXTREME;
     if constexpr (DT == S3A_F32 || DT == S3A_BF16) {
       auto fetch = [&](int rel, RawVec& r) { Planes<DT>::fetch(pl, td.begin + rel, sh.n_points, r); };
-      auto body = [&](RawVec& r, int rel0) { gn_vector<DT, COST>(sh, P, r, rel0, lo_rel, end_rel, check_finite, a); };
+      auto body = [&](RawVec& r, int rel0) {
+        gn_vector<DT, COST, BEGUN || DT != S3A_F32>(sh, P, r, rel0, lo_rel, end_rel, check_finite, check_extreme, a);
+      };
       pipelined_walk<WG, ITEMS, VEC, RawVec, BEGUN>(end_rel, fetch, body, first);
     } else {
-      // depth input whose tile spans frames: unprojected per element (DepthPlanes::load)
+      // depth input whose tile spans frames, or whose pair holds extreme values: a point at a time
       const float tau = sh.tau, delta = sh.delta_f;
       const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
       span_walk<DT, WG, ITEMS>(sh, pl, td, [&](float (&x)[7], bool in) {
-        const bool keep = in && (!check_finite || finite7(x));
+        const bool keep = in && (!check_finite || finite7(x)) && (!check_extreme || (x[6] >= tau && x[6] > 0.0f));
 #pragma unroll
         for (int j = 0; j < 7; ++j) x[j] = keep ? x[j] : 0.0f;
         const float w = x[6] >= tau ? x[6] : 0.0f;
@@ -1015,7 +1061,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
 template <int DT, int WG, int ITEMS, bool BEGUN>
 __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
                                                 typename DepthPlanes<DT>::Raw& first,
-                                                double (&a)[NSTAT], int& nvalid, int& nbad) {
+                                                double (&a)[NSTAT], int& nvalid, int& nbad, ExtremeSeen& extreme) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC;
   const DepthCam& cp = src.cp;
@@ -1044,6 +1090,7 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
       const bool valid = in && fin && c >= tau;
       nvalid += valid ? 1 : 0;
       nbad += (in && !fin) ? 1 : 0;
+      extreme.look(in, fmaxf(fabsf(d[0][e]), fabsf(d[1][e])));
       const float w = valid ? c : 0.0f;
       if (!fin) {  // (a finite pixel of weight zero adds nothing whatever its coordinates)
 #pragma unroll
@@ -1089,8 +1136,10 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
 // FP32 precision), integer counts, DPP wavefront reduction.
 template <int DT, int WG, int ITEMS, bool BEGUN>
 __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td,
-                                   typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out) {
+                                   typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out,
+                                   int32_t* extreme_out) {
   constexpr int VEC = Planes<DT>::VEC;
+  ExtremeSeen extreme{DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16 ? EXTREME / PLAIN_RAY : EXTREME};
   double a[NSTAT];
 #pragma unroll
   for (int j = 0; j < NSTAT; ++j) a[j] = 0.0;
@@ -1099,7 +1148,8 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
     if (pl.frame >= 0) {
-      tile_moments_depth_frame<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, a, nvalid, nbad);
+      tile_moments_depth_frame<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, a, nvalid, nbad, extreme);
+      extreme.mark(extreme_out);
       a[17] = (double)nvalid;
       a[18] = (double)nbad;
       block_store_f64<WG, NSTAT>(a, red, out);
@@ -1112,6 +1162,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
     const bool valid = in && fin && x[6] >= tau;
     nvalid += valid ? 1 : 0;
     nbad += (in && !fin) ? 1 : 0;
+    extreme.look(in, fmaxf(max3_abs(x[0], x[1], x[2]), max3_abs(x[3], x[4], x[5])));
 #pragma unroll
     for (int j = 0; j < 7; ++j) x[j] = valid ? x[j] : 0.0f;
     const double w = x[6];
@@ -1141,6 +1192,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
   } else {
     span_walk<DT, WG, ITEMS>(sh, pl, td, point);
   }
+  extreme.mark(extreme_out);
   a[17] = (double)nvalid;
   a[18] = (double)nbad;
   block_store_f64<WG, NSTAT>(a, red, out);
@@ -1173,14 +1225,16 @@ __device__ inline void tile_cost(const Shape& sh, const SrcCtx<DT>& pl, const Ti
   block_store_f64<WG, 3>(acc, red, out);
 }
 
-// BEGUN: first holds the lane's first vector, its loads issued (tile_begin).
+// extreme: the pair's flag, which a moments pass sets. BEGUN: first holds the lane's first
+// vector, its loads issued (tile_begin).
 template <int DT, int MODE, int WG, int ITEMS, bool BEGUN = false>
 __device__ inline void tile_body(const Shape& sh, const SrcCtx<DT>& pl, const TileDesc& td, const PointParams& P,
-                                 typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out) {
+                                 typename TileRaw<DT>::type& first, double (*red)[NSTAT], double* out,
+                                 int32_t* extreme = nullptr) {
   if constexpr (MODE == MODE_GN || MODE == MODE_GN_NC) {
     tile_gn<DT, WG, ITEMS, MODE == MODE_GN, BEGUN>(sh, pl, td, P, first, red, out);
   } else if constexpr (MODE == MODE_MOMENTS) {
-    tile_moments<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, red, out);
+    tile_moments<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, red, out, extreme);
   } else {
     static_assert(MODE == MODE_COST, "unknown pass mode");
     tile_cost<DT, WG, ITEMS>(sh, pl, td, P, red, out);

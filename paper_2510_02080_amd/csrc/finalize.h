@@ -30,7 +30,7 @@ __device__ inline bool sim3_finite(const Sim3d& S) {
   return z == 0.0 && S.s > 0.0;
 }
 
-__device__ inline void publish(PointParams* P, const Sim3d& S, const double* c, int active, int nonfinite = 1) {
+__device__ inline void publish(PointParams* P, const Sim3d& S, const double* c, int active, int mask = MASK_NONFINITE) {
   PointParams p;
   for (int i = 0; i < 9; ++i) { p.M[i] = S.s * S.R[i]; p.Mf[i] = (float)p.M[i]; }
   for (int i = 0; i < 3; ++i) {
@@ -43,7 +43,7 @@ __device__ inline void publish(PointParams* P, const Sim3d& S, const double* c, 
   p.scale = 0.0f;
   p.L = 0.0f;
   p.active = active;
-  p.nonfinite = nonfinite;
+  p.mask = mask;
   *P = p;
 }
 
@@ -90,13 +90,14 @@ __device__ inline void assemble_gn_packed(const double* st, double* L, double* g
 
 // Moments pass -> weighted Umeyama start (or the caller's), validity, centre: the
 // pair's state from its summed statistics. Returns whether passes follow.
-__device__ inline bool state_from_moments(const Shape& sh, const s3a_sim3* init, bool bad, const double* s,
+__device__ inline bool state_from_moments(const Shape& sh, const s3a_sim3* init, bool bad, bool extreme, const double* s,
                                           PairState* st) {
   const double nan = __builtin_nan("");
   const int64_t V = (int64_t)s[17], nnf = (int64_t)s[18];
   st->C = s[0];
   st->V = V;
   st->nnf = nnf;
+  st->mask = extreme ? MASK_EXTREME : nnf > 0 ? MASK_NONFINITE : MASK_NONE;
   st->cost_lin = nan;
   for (int i = 0; i < 28; ++i) st->H[i] = nan;
   for (int i = 0; i < 7; ++i) st->g[i] = nan;
@@ -233,8 +234,8 @@ __device__ inline void gather_groups(const double* p, int ntiles, int wv, int nw
 // passes follow to S.more; where none does, and `write`, the outputs.
 enum SolveKind { SOLVE_MOMENTS, SOLVE_GN, SOLVE_ANY };
 template <SolveKind KIND>
-__device__ inline void solve_wave(const Shape& sh, const CallDesc* __restrict__ cd, int k, int done, bool bad, bool write,
-                                  SolveLds& S) {
+__device__ inline void solve_wave(const Shape& sh, const CallDesc* __restrict__ cd, int k, int done, bool bad, bool extreme,
+                                  bool write, SolveLds& S) {
   const int lane = (int)threadIdx.x & 63;
   if (lane < NSTAT) {
     double t = 0.0;
@@ -248,7 +249,7 @@ __device__ inline void solve_wave(const Shape& sh, const CallDesc* __restrict__ 
     double fcost = __builtin_nan("");
     int64_t finl = 0;
     if (KIND == SOLVE_MOMENTS || (KIND == SOLVE_ANY && done == 0)) {
-      more = state_from_moments(sh, cd->init ? cd->init + k : nullptr, bad, S.sums, &S.st);
+      more = state_from_moments(sh, cd->init ? cd->init + k : nullptr, bad, extreme, S.sums, &S.st);
       ended = !more;
     } else if (S.st.status == S3A_PAIR_OK) {
       if (done <= sh.K) {

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(WG, 2) void k_persistent(Shape sh, const CallDesc* 
     const PointParams P = load_params(w.params + j);
     double* out = w.partials + (int64_t)t * NSTAT;
     RawVec first;
-    if (pass == 0) tile_body<DT, MODE_MOMENTS, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
+    if (pass == 0) tile_body<DT, MODE_MOMENTS, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out, &w.sched[j].extreme);
     else if (pass < sh.K) tile_body<DT, MODE_GN_NC, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
     else tile_body<DT, MODE_GN, WG, ITEMS>(sh, SrcCtx<DT>{pl}, td, P, first, red, out);
     if (threadIdx.x == 0) {
@@ -128,11 +128,11 @@ __global__ __launch_bounds__(WG, 2) void k_persistent(Shape sh, const CallDesc* 
         gather_groups(w.partials + (int64_t)sc.tile0 * NSTAT, sc.ntiles, 0, 1, S.part);
         if (pass > 0) set_state_word(&S.st, state_word(w.state + j));
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        solve_wave<SOLVE_ANY>(sh, cd, j, pass, sc.bad != 0, true, S);
+        solve_wave<SOLVE_ANY>(sh, cd, j, pass, sc.bad != 0, sc.extreme != 0, true, S);
         set_state_word(w.state + j, state_word(&S.st));
         stores_done();
         if (threadIdx.x == 0) {
-          publish(w.params + j, S.st.S, S.st.cq, S.more, S.st.nnf > 0 ? 1 : 0);
+          publish(w.params + j, S.st.S, S.st.cq, S.more, S.st.mask);
           arrive[j] = 0u;
           __threadfence();
           __hip_atomic_store(w.flags + j, (uint32_t)(pass + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);

@@ -75,7 +75,7 @@ struct PairSched {
   int32_t tile0;    // first tile
   int32_t ntiles;   // >= 1 (an empty or bad pair gets one empty tile)
   int32_t bad;      // offsets out of order or out of range
-  int32_t pad;
+  int32_t extreme;  // set by the moments pass: a finite value of the pair's points is EXTREME or more
 };
 
 // Per-pair parameters read by the point passes.
@@ -90,8 +90,16 @@ struct PointParams {
   float scale;   // gL (adjoint)
   float L;       // cost (adjoint)
   int32_t active;// 0: skip (pair failed or finished)
-  int32_t nonfinite; // the pair holds NaN/Inf values (validity then checks finiteness)
+  int32_t mask;  // what the passes have to look for: PairMask
 };
+
+// What a pair's points hold, which decides what a Gauss-Newton pass looks for in
+// each: nothing; NaN/Inf values; or also finite values whose squares may leave the
+// FP32 range (a sentinel where a depth is missing): at weight zero they would still give
+// 0 x inf. EXTREME leaves a factor 1e7 to the similarity's scale below that range.
+enum PairMask { MASK_NONE = 0, MASK_NONFINITE = 1, MASK_EXTREME = 2 };
+constexpr float EXTREME = 1e12f;
+constexpr float PLAIN_RAY = 1e4f;  // depth frames whose rays are longer are walked point by point
 
 // FP64 master state per pair.
 struct PairState {
@@ -106,6 +114,8 @@ struct PairState {
   int64_t inl_lin;
   int32_t status;
   int32_t iters;
+  int32_t mask;  // PairMask
+  int32_t pad;
 };
 
 // Per-call pointers read by every kernel of a call.

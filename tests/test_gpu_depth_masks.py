@@ -1,7 +1,7 @@
 """Depth pairs that hold pixels whose points are not finite though their depths
-are (a lost frame's camera): such pixels are invalid wherever they lie, in tiles
-of one frame as in tiles that span two, on every launch path. Against the FP64
-oracle."""
+are (a lost frame's camera, a ray that overflows): such pixels are invalid
+wherever they lie, in tiles of one frame as in tiles that span two, on every
+launch path. Against the FP64 oracle."""
 
 import numpy as np
 import pytest
@@ -73,3 +73,20 @@ def test_lost_translation(side, dtype):
         T, info = run(h, b, flags)
         for k in range(3):
             check_pair(T[k], info[k], refs[k], where=f"{side} {dtype} pair {k} flags {flags}", dr=DR_DEPTH)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_ray_that_overflows(dtype):
+    """A pixel of ordinary depth for its type, 1e28, whose ray takes it past the
+    FP32 range, below the confidence threshold as the rest of its frame."""
+    b = batch(dtype)
+    n = HW[0] * HW[1]
+    b.pairs[0]["p"][1]["fx"] = 1e-12
+    c, d = (0x3f00, 0x6e01) if dtype == "bf16" else (0.5, 1e28)  # 0.5 and 1.0e28
+    b.c[n:2 * n] = c
+    b.dp[70000] = d
+    refs = [oracle_pair(b, k) for k in range(3)]
+    assert refs[0]["status"] == 0
+    refs[0]["n_nonfinite"] += 1  # finite in FP64, not in the FP32 that the points are given in
+    for h, flags in handles():
+        T, info = run(h, b, flags)
+        for k in range(3):
+            check_pair(T[k], info[k], refs[k], where=f"{dtype} pair {k} flags {flags}", dr=DR_DEPTH)
