@@ -65,12 +65,12 @@ __device__ inline bool camera_plain(const s3a_camera& c, int width, int rows) {
 }
 
 // Tile j of a pair's range [a, b); depth: the pair's frames, or null. Frames narrower
-// than a vector count as spanned (their pixels go one at a time: see DepthWalk), and so
-// do frames whose camera is lost or out of all scale: the walk of a frame masks a pixel by
+// than a vector of vec pixels count as spanned (see DepthWalk), and so do frames whose
+// camera is lost or out of all scale: the walk of a frame masks a pixel by
 // its depths, which such a camera takes to NaN all the same, while the spanning walk
 // masks the points themselves.
 __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, int ntiles, int j, int64_t T,
-                                     const s3a_depth_pair* depth) {
+                                     const s3a_depth_pair* depth, int vec) {
   const int64_t b0 = a & ~(TILE_ALIGN - 1);
   TileDesc t;
   t.pair = pair;
@@ -81,11 +81,12 @@ __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, 
     t.begin = b0 + (int64_t)j * T;
     t.end = t.begin + T < b ? t.begin + T : b;
     t.lo = a;
-    if (depth && depth->width >= 8 && depth->frame_pixels >= depth->width) {
+    if (depth && depth->width >= vec && depth->frame_pixels >= depth->width) {
       const int64_t first = t.begin > a ? t.begin : a;
       const int f0 = (int)((first - a) / depth->frame_pixels), f1 = (int)((t.end - 1 - a) / depth->frame_pixels);
-      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first && camera_plain(depth->p[f0], depth->width, depth->frame_pixels / depth->width) &&
-          camera_plain(depth->q[f0], depth->width, depth->frame_pixels / depth->width))
+      const int rows = depth->frame_pixels / depth->width;
+      if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first &&
+          camera_plain(depth->p[f0], depth->width, rows) && camera_plain(depth->q[f0], depth->width, rows))
         t.frame = f0;
     }
   } else {
@@ -163,7 +164,8 @@ __global__ __launch_bounds__(SCHED_WG) void k_sched_tiles(Shape sh, CallDesc c, 
       else hi = mid - 1;
     }
     const int64_t a = any_bad ? 0 : c.offsets[lo], b = any_bad ? 0 : c.offsets[lo + 1];
-    w.tiles[t] = make_tile(a, b, lo, tile0[lo], tile0[lo + 1] - tile0[lo], t - tile0[lo], T, c.depth ? c.depth + lo : nullptr);
+    w.tiles[t] = make_tile(a, b, lo, tile0[lo], tile0[lo + 1] - tile0[lo], t - tile0[lo], T,
+                           c.depth ? c.depth + lo : nullptr, sh.vec);
   }
 }
 
@@ -222,7 +224,8 @@ __global__ void k_sched_fill(Shape sh, const s3a_depth_pair* depth, Work w) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= sh.n_pairs) return;
   const PairSched s = w.sched[k];
-  for (int j = 0; j < s.ntiles; ++j) w.tiles[s.tile0 + j] = make_tile(s.a, s.b, k, s.tile0, s.ntiles, j, sh.tile_elems, depth ? depth + k : nullptr);
+  for (int j = 0; j < s.ntiles; ++j) w.tiles[s.tile0 + j] = make_tile(s.a, s.b, k, s.tile0, s.ntiles, j, sh.tile_elems,
+                                                                    depth ? depth + k : nullptr, sh.vec);
 }
 
 __global__ void k_depth_prep(Shape sh, const CallDesc* __restrict__ cd, Work w) {

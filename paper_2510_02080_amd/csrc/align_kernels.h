@@ -344,12 +344,6 @@ __device__ inline DepthCam load_cam_uniform(const DepthCam* c) {
   return r;
 }
 
-__device__ inline void unproject(const DepthCam& c, float col, float row, float d, float* x) {
-  const float rx = fmaf(col, c.ifx, c.ox), ry = fmaf(row, c.ify, c.oy);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) x[i] = fmaf(d, fmaf(c.R[3 * i], rx, fmaf(c.R[3 * i + 1], ry, c.R[3 * i + 2])), c.t[i]);
-}
-
 // q = floor(x / m) for 0 <= x < 2^31, m >= 1: a float estimate, corrected.
 __device__ inline int div_floor(int x, int m, float inv_m) {
   int q = (int)((float)x * inv_m);
@@ -412,56 +406,6 @@ struct DepthPlanes {
           d[j][i] = __uint_as_float(r[j][i]);
         }
       }
-  }
-
-  // frame, row and column of element g0 (elements before the pair count as its first pixel)
-  __device__ static inline void position(const SrcCtx<DT>& s, int64_t g0, int& f, int& row, int& col) {
-    int j = (int)(g0 - s.a);
-    j = j < 0 ? 0 : j;
-    f = div_floor(j, s.frame_pixels, s.inv_frame);
-    const int pin = j - f * s.frame_pixels;
-    row = div_floor(pin, s.width, s.inv_width);
-    col = pin - row * s.width;
-  }
-
-  // the next pixel (row-major, frame after frame)
-  __device__ static inline void advance(const SrcCtx<DT>& s, int& f, int& row, int& col) {
-    if (++col == s.width) {
-      col = 0;
-      if (++row == s.rows) {
-        row = 0;
-        ++f;
-      }
-    }
-  }
-
-  // The vector's elements one at a time, each unprojected with its own frame's
-  // cameras: point(x, rel) takes (p, q, c) and the element's offset from the vector's
-  // start. For the few tiles that span frames: kept small in registers (they set the
-  // occupancy of the kernels that hold it), not fast.
-  template <typename Point>
-  __device__ static inline void each(const SrcCtx<DT>& s, int64_t g0, int64_t n, Point&& point) {
-    Raw r;
-    fetch(s, g0, n, r);
-    int f, row, col;
-    position(s, g0, f, row, col);
-#pragma unroll 1
-    for (int e = 0; e < VEC; ++e) {
-      const int k = BF ? e >> 1 : e;
-      float d[3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const uint32_t u = k == 0 ? r[j][0] : k == 1 ? r[j][1] : k == 2 ? r[j][2] : r[j][3];
-        d[j] = __uint_as_float(BF ? ((e & 1) ? (u & 0xffff0000u) : (u << 16)) : u);
-      }
-      const int fc = f < s.n_frames ? f : s.n_frames - 1;
-      float x[7];
-      unproject(s.dp->p[fc], (float)col, (float)row, d[0], x);
-      unproject(s.dp->q[fc], (float)col, (float)row, d[1], x + 3);
-      x[6] = d[2];
-      point(x, e);
-      if (g0 + e >= s.a) advance(s, f, row, col);
-    }
   }
 };
 
@@ -741,8 +685,9 @@ struct CamForm {
 
 // Calls pixel(e, hp, hq, col) for the VEC pixels from (row, col), hp and hq the
 // row shares of the forms: one row's where no lane of the wavefront crosses a row
-// end, else the first or the next row's, chosen per pixel.
-template <int VEC, typename Pixel>
+// end, else the first or the next row's, chosen per pixel. NARROW: frames narrower than a
+// vector too, where each pixel forms its own row's share.
+template <int VEC, bool NARROW = false, typename Pixel>
 __device__ inline void walk_pixels(int row, int col, int width, const CamForm& P, const CamForm& Q, Pixel&& pixel) {
   float hp[3], hq[3];
   const float fr = (float)row, fc = (float)col;
@@ -752,6 +697,18 @@ __device__ inline void walk_pixels(int row, int col, int width, const CamForm& P
   if (__builtin_amdgcn_ballot_w64(cross) == 0ull) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) pixel(e, hp, hq, fc + (float)e);
+  } else if (NARROW && width < VEC) {
+    int r = row, c = col;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      P.row((float)r, hp);
+      Q.row((float)r, hq);
+      pixel(e, hp, hq, (float)c);
+      if (++c == width) {
+        c = 0;
+        ++r;
+      }
+    }
   } else {
     float hp1[3], hq1[3];
     P.row(fr + 1.0f, hp1);
@@ -778,23 +735,14 @@ __device__ inline void walk_pixels(int row, int col, int width, const CamForm& P
 // here. Bound by issue: with cameras and rows taken per segment instead of per element,
 // 150 pairs of one to three 160 x 120 BF16 frames 722 -> 413 us a call, 60 pairs of
 // 300 x 200 779 -> 475, and 256 pairs of 518 x 392 FP32, whose last tiles these are,
-// 1863 -> 1681. One element at a time remains for frames narrower than a
-// vector, where one may hold several row ends.
+// 1863 -> 1681. So are frames narrower than a vector (13 M pixels in rows of 1 to 3,
+// FP32, 700 us a call; an element at a time 1118, 615 when the one-frame walk took them
+// element-wise too; BF16 rows of 1 to 7 590, 1185 and 670).
 template <int DT, int WG, int ITEMS, typename Point>
 __device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const TileDesc& td, Point&& point) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC, STRIDE = WG * VEC;
   const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin), at = (int)(td.begin - s.a);
-  if (s.width < VEC) {
-#pragma unroll 1
-    for (int it = 0; it < ITEMS; ++it) {
-      const int rel0 = (it * WG + (int)threadIdx.x) * VEC;
-      if (rel0 >= end_rel) break;
-      L::each(s, td.begin + rel0, sh.n_points,
-              [&](float (&x)[7], int e) { point(x, rel0 + e >= lo_rel && rel0 + e < end_rel); });
-    }
-    return;
-  }
   int seg = lo_rel > 0 ? lo_rel : 0;
 #pragma unroll 1
   while (seg < end_rel) {
@@ -813,8 +761,8 @@ __device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const Til
       float d[3][VEC];
       L::unpack(r, d);
       const int j = at + rel0 - f * s.frame_pixels;  // above -VEC: the vector may begin in the frame before
-      const int row = j < 0 ? -1 : div_floor(j, s.width, s.inv_width);
-      walk_pixels<VEC>(row, j - row * s.width, s.width, fp, fq,
+      const int row = j < 0 ? ~div_floor(~j, s.width, s.inv_width) : div_floor(j, s.width, s.inv_width);
+      walk_pixels<VEC, true>(row, j - row * s.width, s.width, fp, fq,
                        [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
         const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
         float x[7];

@@ -253,6 +253,7 @@ Shape make_shape(const s3a_align_desc* d, const LaunchCfg& lc) {
   sh.delta_f = (float)d->huber_delta;
   sh.flags = d->flags;
   sh.tile_elems = (int32_t)tile_elems(d->dtype, lc);
+  sh.vec = (d->dtype & 1) ? 8 : 4;
   return sh;
 }
 

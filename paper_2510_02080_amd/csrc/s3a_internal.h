@@ -151,6 +151,7 @@ struct Shape {
   double delta;
   uint32_t flags;
   int32_t tile_elems;
+  int32_t vec;  // elements of a 16-byte vector of the planes
 };
 
 // Workspace pointers (device).
