@@ -33,8 +33,7 @@ __device__ inline bool depth_prep(const s3a_depth_pair& src, int64_t n, DepthPai
   dp.frame_pixels = HW;
   dp.n_frames = nf;
   dp.inv_width = 1.0f / (float)W;
-  dp.inv_frame = 1.0f / (float)HW;
-  dp.pad[0] = dp.pad[1] = 0;
+  dp.pad[0] = dp.pad[1] = dp.pad[2] = 0;
   for (int f = 0; f < DEPTH_MAX_FRAMES; ++f) {
     const s3a_camera* in[2] = {src.p + f, src.q + f};
     DepthCam* cam[2] = {dp.p + f, dp.q + f};

@@ -47,7 +47,7 @@ struct DepthCtx {
   const DepthPair* dp;
   int64_t a;            // first element of the pair
   int width, rows, frame_pixels, n_frames;
-  float inv_width, inv_frame;
+  float inv_width;
   int frame;            // the tile's frame when it lies in one, else -1
   DepthCam cp, cq;      // that frame's cameras (valid when frame >= 0)
 };
@@ -326,6 +326,9 @@ __device__ inline TileDesc load_tile(const TileDesc* p) {
   return r;
 }
 
+// Where a tile's pair starts in it (past its head in the pair's first tile; else 0).
+__device__ inline int tile_lo(const TileDesc& td) { return td.lo > td.begin ? (int)(td.lo - td.begin) : 0; }
+
 // Depth input: three planes (d_p, d_q, c), the pixel's frame, row and column
 // from its index in the pair, and each side unprojected with its camera:
 // x = R (d ((col, row) * inv_f + o, 1)) + t. Elements before the pair's start
@@ -344,14 +347,19 @@ __device__ inline DepthCam load_cam_uniform(const DepthCam* c) {
   return r;
 }
 
-// q = floor(x / m) for 0 <= x < 2^31, m >= 1: a float estimate, corrected.
+// q = floor(x / m) for 0 <= x < 2^31, m >= 1 and quotients below 2^22: a float estimate,
+// corrected (unsigned: the next multiple may pass 2^31).
 __device__ inline int div_floor(int x, int m, float inv_m) {
-  int q = (int)((float)x * inv_m);
-  q -= (q * m > x) ? 1 : 0;
-  q += ((q + 1) * m <= x) ? 1 : 0;
-  q -= (q * m > x) ? 1 : 0;
-  return q;
+  const unsigned ux = (unsigned)x, um = (unsigned)m;
+  unsigned q = (unsigned)((float)x * inv_m);
+  q -= (q * um > ux) ? 1u : 0u;
+  q += ((q + 1u) * um <= ux) ? 1u : 0u;
+  q -= (q * um > ux) ? 1u : 0u;
+  return (int)q;
 }
+
+// floor(x / m) for x of either sign (an element before the frame's first counts back)
+__device__ inline int row_of(int x, int m, float inv_m) { return x < 0 ? ~div_floor(~x, m, inv_m) : div_floor(x, m, inv_m); }
 
 template <int DT>
 struct DepthPlanes {
@@ -429,7 +437,6 @@ __device__ inline SrcCtx<DT> make_src(const void* const* pl, const Work& w, cons
     s.frame_pixels = uniform_i32(s.dp->frame_pixels);
     s.n_frames = uniform_i32(s.dp->n_frames);
     s.inv_width = uniform_f32(s.dp->inv_width);
-    s.inv_frame = uniform_f32(s.dp->inv_frame);
     s.frame = td.frame;
     if (s.frame >= 0) {
       s.cp = load_cam_uniform(s.dp->p + s.frame);
@@ -635,11 +642,9 @@ struct DepthWalk {
   int row, col, drow, dcol, width;
   __device__ inline DepthWalk(const SrcCtx<DT>& s, const TileDesc& td, int first, int stride) {
     width = s.width;
-    const int back = 64 * width;  // a tile starts at most 63 elements before the pair
-    const int j = (int)(td.begin + first - td.lo) - s.frame * s.frame_pixels + back;
-    row = div_floor(j, width, s.inv_width);
+    const int j = (int)(td.begin + first - td.lo - (int64_t)s.frame * s.frame_pixels);
+    row = row_of(j, width, s.inv_width);
     col = j - row * width;
-    row -= 64;
     drow = uniform_i32(div_floor(stride, width, s.inv_width));
     dcol = stride - drow * width;
   }
@@ -693,7 +698,7 @@ __device__ inline void walk_pixels(int row, int col, int width, const CamForm& P
   const float fr = (float)row, fc = (float)col;
   P.row(fr, hp);
   Q.row(fr, hq);
-  const bool cross = col + VEC > width;
+  const bool cross = col > width - VEC;
   if (__builtin_amdgcn_ballot_w64(cross) == 0ull) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) pixel(e, hp, hq, fc + (float)e);
@@ -716,7 +721,7 @@ __device__ inline void walk_pixels(int row, int col, int width, const CamForm& P
     const float fw = (float)width;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      const bool over = col + e >= width;
+      const bool over = col >= width - e;
       float sp[3], sq[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -742,13 +747,15 @@ template <int DT, int WG, int ITEMS, typename Point>
 __device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const TileDesc& td, Point&& point) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC, STRIDE = WG * VEC;
-  const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin), at = (int)(td.begin - s.a);
+  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+  const int64_t at = td.begin - s.a;
   int seg = lo_rel > 0 ? lo_rel : 0;
 #pragma unroll 1
   while (seg < end_rel) {
-    int f = uniform_i32(div_floor(at + seg, s.frame_pixels, s.inv_frame));
-    f = f < s.n_frames ? f : s.n_frames - 1;
-    const int64_t here = (int64_t)(f + 1) * s.frame_pixels - at;  // where the frame ends
+    int f = 0;  // the frame of at + seg: a pair has few
+    while (f + 1 < s.n_frames && (int64_t)(f + 1) * s.frame_pixels <= at + seg) ++f;
+    const int from = (int)((int64_t)f * s.frame_pixels - at);  // where the frame starts, and ends
+    const int64_t here = (int64_t)(f + 1) * s.frame_pixels - at;
     const int seg_end = f + 1 < s.n_frames && here < end_rel ? (int)here : end_rel;
     const DepthCam cp = load_cam_uniform(s.dp->p + f), cq = load_cam_uniform(s.dp->q + f);
     const CamForm fp(cp.R, cp), fq(cq.R, cq);
@@ -760,8 +767,8 @@ __device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const Til
       L::fetch(s, td.begin + rel0, sh.n_points, r);
       float d[3][VEC];
       L::unpack(r, d);
-      const int j = at + rel0 - f * s.frame_pixels;  // above -VEC: the vector may begin in the frame before
-      const int row = j < 0 ? ~div_floor(~j, s.width, s.inv_width) : div_floor(j, s.width, s.inv_width);
+      const int j = rel0 - from;  // above -VEC: the vector may begin in the frame before
+      const int row = row_of(j, s.width, s.inv_width);
       walk_pixels<VEC, true>(row, j - row * s.width, s.width, fp, fq,
                        [&](int e, const float (&hp)[3], const float (&hq)[3], float fc) {
         const float rxp = fmaf(fc, fp.ifx, fp.ox), rxq = fmaf(fc, fq.ifx, fq.ox);
@@ -838,7 +845,7 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
   }
   const float tau = sh.tau, delta = sh.delta_f;
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
-  const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
   const bool check_finite = P.mask != MASK_NONE;
   auto fetch = [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); };
   DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
@@ -970,7 +977,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
     }
   }
   if (P.active) {
-    const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
+    const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
     const bool check_finite = P.mask != MASK_NONE, check_extreme = P.mask == MASK_EXTREME;
     if constexpr (DT == S3A_F32 || DT == S3A_BF16) {
       auto fetch = [&](int rel, RawVec& r) { Planes<DT>::fetch(pl, td.begin + rel, sh.n_points, r); };
@@ -1015,7 +1022,7 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
   const DepthCam& cp = src.cp;
   const DepthCam& cq = src.cq;
   const float tau = sh.tau;
-  const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
   DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
   const CamForm fp(cp.R, cp), fq(cq.R, cq);
   auto body = [&](const typename L::Raw& raw, int rel0) {
@@ -1093,7 +1100,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
   for (int j = 0; j < NSTAT; ++j) a[j] = 0.0;
   int nvalid = 0, nbad = 0;
   const float tau = sh.tau;
-  const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
     if (pl.frame >= 0) {
       tile_moments_depth_frame<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, a, nvalid, nbad, extreme);
@@ -1153,7 +1160,7 @@ __device__ inline void tile_cost(const Shape& sh, const SrcCtx<DT>& pl, const Ti
   constexpr int VEC = Planes<DT>::VEC;
   double acc[3] = {0.0, 0.0, 0.0};
   if (P.active) {
-    const int lo_rel = (int)(td.lo - td.begin), end_rel = (int)(td.end - td.begin);
+    const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
 #pragma unroll 1
     for (int it = 0; it < ITEMS; ++it) {
       const int rel0 = (it * WG + (int)threadIdx.x) * VEC;

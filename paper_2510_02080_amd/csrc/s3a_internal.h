@@ -54,8 +54,8 @@ struct DepthCam {
 // cameras of each shared frame.
 struct DepthPair {
   int32_t width, rows, frame_pixels, n_frames;
-  float inv_width, inv_frame;  // 1/width, 1/frame_pixels (division estimates, corrected exactly)
-  int32_t pad[2];
+  float inv_width;  // 1/width (a division estimate, corrected exactly)
+  int32_t pad[3];
   DepthCam p[DEPTH_MAX_FRAMES];
   DepthCam q[DEPTH_MAX_FRAMES];
 };
