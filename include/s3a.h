@@ -269,7 +269,7 @@ int s3a_align_pairs_backward(s3a_handle* h, const s3a_align_desc* desc, const s3
                              float* gpx, float* gpy, float* gpz, float* gqx, float* gqy, float* gqz,
                              float* gc, double* gxi, s3a_stream stream);
 /* The same, and entries outside every pair's range are written as zero (all of them when
- * the offsets are invalid), so that the arrays need no clearing beforehand. */
+ * the offsets are invalid or there are no pairs), so that the arrays need no clearing beforehand. */
 int s3a_align_pairs_backward_zeroed(s3a_handle* h, const s3a_align_desc* desc, const s3a_sim3* S,
                                     const double* xi, const double* L, const double* C, const double* gL,
                                     float* gpx, float* gpy, float* gpz, float* gqx, float* gqy, float* gqz,
@@ -305,7 +305,7 @@ int s3a_align_pairs_implicit_backward(s3a_handle* h, const s3a_align_desc* desc,
                                       float* gqx, float* gqy, float* gqz, float* gc, double* v_out,
                                       int32_t* status_out, s3a_stream stream);
 /* The same, and entries outside every pair's range are written as zero (all of them when
- * the offsets are invalid). */
+ * the offsets are invalid or there are no pairs). */
 int s3a_align_pairs_implicit_backward_zeroed(s3a_handle* h, const s3a_align_desc* desc, const s3a_sim3* S,
                                              const double* gS, uint32_t flags, float* gpx, float* gpy, float* gpz,
                                              float* gqx, float* gqy, float* gqz, float* gc, double* v_out,

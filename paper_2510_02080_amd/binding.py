@@ -290,12 +290,10 @@ class Handle:
         N = pm.n_points
         Np = (N + 3) // 4 * 4  # row stride keeping every plane 16-byte aligned
         dev = pm.device
-        # the library writes every entry: those inside the pairs, and zeros outside (a
-        # call without pairs writes nothing)
-        alloc = torch.empty if pm.n_pairs else torch.zeros
-        gp = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
-        gq = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
-        gc = alloc(N, dtype=torch.float32, device=dev) if need[2] else None
+        # the library writes every entry: those inside the pairs, and zeros outside
+        gp = torch.empty((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
+        gq = torch.empty((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
+        gc = torch.empty(N, dtype=torch.float32, device=dev) if need[2] else None
         gxi = torch.empty((pm.n_pairs, 7), dtype=torch.float64, device=dev) if need[3] else None
         d = pm.desc(tau, delta, 0)
         gps = [_ptr(gp[i]) if gp is not None else None for i in range(3)]
@@ -313,10 +311,9 @@ class Handle:
         N = pm.n_points
         Np = (N + 3) // 4 * 4
         dev = pm.device
-        alloc = torch.empty if pm.n_pairs else torch.zeros
-        gp = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
-        gq = alloc((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
-        gc = alloc(N, dtype=torch.float32, device=dev) if need[2] else None
+        gp = torch.empty((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[0] else None
+        gq = torch.empty((3, Np), dtype=torch.float32, device=dev)[:, :N] if need[1] else None
+        gc = torch.empty(N, dtype=torch.float32, device=dev) if need[2] else None
         v = torch.empty((pm.n_pairs, 7), dtype=torch.float64, device=dev)
         status = torch.empty(pm.n_pairs, dtype=torch.int32, device=dev)
         d = pm.desc(tau, delta, 0)

@@ -655,6 +655,13 @@ int s3a_align_cost(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, co
   return S3A_OK;
 }
 
+// A call without pairs has no schedule, and every entry lies outside them.
+static int zero_planes(s3a_handle* h, float* const (&planes)[7], int64_t n, hipStream_t st) {
+  for (float* p : planes)
+    if (p && n > 0) S3A_TRY(launch_fill_zero(reinterpret_cast<uint32_t*>(p), n, st));
+  return S3A_OK;
+}
+
 static int backward_impl(s3a_handle* h, bool zero_rest, const s3a_align_desc* d, const s3a_sim3* S, const double* xi,
                              const double* L, const double* C, const double* gL, float* gpx, float* gpy, float* gpz,
                              float* gqx, float* gqy, float* gqz, float* gc, double* gxi, s3a_stream stream) {
@@ -665,9 +672,9 @@ static int backward_impl(s3a_handle* h, bool zero_rest, const s3a_align_desc* d,
   float* gr[7] = {gpx, gpy, gpz, gqx, gqy, gqz, gc};
   for (float* p : gr)
     if (p && !aligned16(p)) return S3A_EINVAL;
-  if (d->n_pairs == 0) return S3A_OK;
   DeviceGuard g(h->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (d->n_pairs == 0) return zero_rest ? zero_planes(h, gr, d->n_points, st) : S3A_OK;
   S3A_ORDERED(h, st);
   const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
   Shape sh = make_shape(d, lc);
@@ -706,9 +713,9 @@ static int implicit_backward_impl(s3a_handle* h, bool zero_rest, const s3a_align
   float* gr[7] = {gpx, gpy, gpz, gqx, gqy, gqz, gc};
   for (float* p : gr)
     if (p && !aligned16(p)) return S3A_EINVAL;
-  if (d->n_pairs == 0) return S3A_OK;
   DeviceGuard g(h->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (d->n_pairs == 0) return zero_rest ? zero_planes(h, gr, d->n_points, st) : S3A_OK;
   S3A_ORDERED(h, st);
   const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
   Shape sh = make_shape(d, lc);
