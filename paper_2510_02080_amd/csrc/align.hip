@@ -394,7 +394,7 @@ static hipError_t launch_pass_t(const LaunchCfg& lc, const Shape& sh, const Call
     return hipGetLastError();                                                                               \
   }
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
-    if (lc.wg == 256 && lc.items == 16 && lc.occupancy == 0) {  // the untuned depth shape
+    if (lc.wg == 256 && lc.items == 16 && lc.occupancy == 0 && grid < GRID_THREADS / 256) {  // the untuned depth shape
       hipLaunchKernelGGL((k_pass<DT, MODE, 256, 16, true>), dim3(grid), dim3(256), 0, st, sh, cd, w, tile_lo, tile_hi);
       return hipGetLastError();
     }
@@ -479,9 +479,13 @@ hipError_t launch_solve_last(const Shape& sh, const CallDesc* cd, const Work& w,
 
 hipError_t launch_finalize(const Shape& sh, const CallDesc* cd, const Work& w, int pass, int32_t pair_lo, int32_t n,
                            hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(256), 0, st, sh, cd, w, pass, pair_lo);
-  return hipGetLastError();
+  for (int32_t k = 0; k < n; k += (int32_t)(GRID_THREADS / 256)) {
+    const int32_t m = std::min(n - k, (int32_t)(GRID_THREADS / 256));
+    hipLaunchKernelGGL(k_finalize, dim3(m), dim3(256), 0, st, sh, cd, w, pass, pair_lo + k);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_prep(const Shape& sh, const CallDesc* cd, const Work& w, int adjoint, hipStream_t st) {

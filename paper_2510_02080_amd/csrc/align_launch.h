@@ -15,6 +15,9 @@ struct LaunchCfg {
 // BF16 planes (xyz or depth) load 8 elements per 16 bytes, FP32 ones 4.
 inline int vec_of(int dtype) { return (dtype == S3A_BF16 || dtype == DT_DEPTH_BF16) ? 8 : 4; }
 inline int64_t tile_elems(int dtype, const LaunchCfg& lc) { return (int64_t)lc.wg * lc.items * vec_of(dtype); }
+// Threads of one launch (HIP holds them below 2^32).
+constexpr int64_t GRID_THREADS = 1ll << 31;
+
 // Upper bound of the tile count of any batch (see k_sched).
 inline int64_t max_tiles(int64_t n_points, int n_pairs, int64_t tile) { return n_points / tile + 2 * (int64_t)n_pairs + 1; }
 

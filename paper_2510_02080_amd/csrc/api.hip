@@ -271,10 +271,11 @@ CallDesc make_call(const s3a_align_desc* d) {
 // argument, stores it there for the kernels that follow.
 CallDesc* desc_slot(s3a_handle* h) { return h->desc; }
 
-// Occupancy 0: one workgroup per tile (the hardware balances the tail);
-// otherwise a fixed number of workgroups per compute unit loops over the tiles.
+// Occupancy 0: one workgroup per tile (the hardware balances the tail), up to what a
+// launch holds (the kernels loop over what is left); otherwise a fixed number of
+// workgroups per compute unit loops over the tiles.
 int grid_for(s3a_handle* h, const LaunchCfg& lc, int64_t tiles) {
-  const int64_t g = lc.occupancy == 0 ? tiles
+  const int64_t g = lc.occupancy == 0 ? std::min<int64_t>(tiles, GRID_THREADS / lc.wg)
                                       : std::min<int64_t>(tiles, (int64_t)lc.occupancy * h->n_cu * (256 / std::min(lc.wg, 256)));
   return (int)std::max<int64_t>(g, 1);
 }
