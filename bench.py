@@ -275,7 +275,7 @@ def main():
         kp, _ = kernel_ms(stepp, args.steps)
         Sp, ibp = h.align_pairs(pm, b2.tau, b2.delta, b2.iters, flags=s3a.FLAG_PERSISTENT)
         torch.cuda.synchronize()
-        if retune:  # the handle keeps one tuned shape per size: the per-pass path's again
+        if retune:  # calls of kinds that are not tuned take the shape found last: the per-pass path's again
             h.autotune(pm, b2.tau, b2.delta, b2.iters)
         # bit for bit equal only when both paths use the same tile size
         same = bool(torch.equal(Sp, S)) and bool(torch.equal(ibp, ib))

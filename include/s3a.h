@@ -438,15 +438,19 @@ int s3a_correct_points(s3a_handle* h, int64_t n_corr, const int64_t* src, const 
                        const float* wx, const float* wy, const float* wz, int64_t n_sparse, float* sx, float* sy,
                        float* sz, unsigned long long* n_skipped, s3a_stream stream);
 
-/* Time candidate launch shapes on this batch and keep the fastest for its
- * (dtype, size class). Synchronises the stream. best may be NULL. */
+/* Time candidate launch shapes on this batch and keep the fastest for calls of its
+ * kind: dtype, size classes of points and of pairs, persistent launch or not.
+ * Calls of a kind that was not tuned take the shape kept last for their dtype
+ * and points, except small ones that do better untuned. Synchronises the
+ * stream. best may be NULL. */
 int s3a_autotune(s3a_handle* h, const s3a_align_desc* desc, s3a_tuning* best, s3a_stream stream);
 /* The same for depth-map input: the shape is kept for depth-map calls of this
- * plane type and size class, apart from stored-point calls (the pass kernels do
- * different work per byte). Errors as s3a_align_depth_pairs. */
+ * kind, apart from stored-point calls (the pass kernels do different work per
+ * byte). Errors as s3a_align_depth_pairs. */
 int s3a_autotune_depth(s3a_handle* h, const s3a_depth_desc* desc, s3a_tuning* best, s3a_stream stream);
 /* Force one shape for every call on planes of dtype, depth-map input included. */
 int s3a_set_tuning(s3a_handle* h, int32_t dtype, const s3a_tuning* t); /* t = NULL: back to automatic */
+/* The shape forced for dtype, or kept last for calls of n_points, or the untuned one. */
 int s3a_get_tuning(s3a_handle* h, int32_t dtype, int64_t n_points, s3a_tuning* t);
 
 /*

@@ -402,7 +402,7 @@ class Handle:
 
     def autotune_depth(self, dm, tau, delta=0.05, iters=10, flags=0):
         """autotune for depth-map input (DepthPointmaps): the shape is kept for
-        depth-map calls of that plane type and size class."""
+        depth-map calls of that kind."""
         best = Tuning()
         d = dm.desc(tau, delta, iters, flags)
         _check(self.lib.s3a_autotune_depth(self.h, ctypes.byref(d), ctypes.byref(best), _stream(dm.device)), self.h)

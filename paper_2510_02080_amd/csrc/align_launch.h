@@ -2,15 +2,9 @@
 #pragma once
 
 #include "s3a_internal.h"
+#include "tuning.h"
 
 namespace s3a {
-
-struct LaunchCfg {
-  int wg = 256;
-  int items = 4;
-  int occupancy = 4;  // persistent workgroups per CU
-  int window = 0;     // pairs per window in the persistent launch (0: all)
-};
 
 // BF16 planes (xyz or depth) load 8 elements per 16 bytes, FP32 ones 4.
 inline int vec_of(int dtype) { return (dtype == S3A_BF16 || dtype == DT_DEPTH_BF16) ? 8 : 4; }

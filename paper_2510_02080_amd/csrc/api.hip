@@ -15,16 +15,6 @@
 
 using namespace s3a;
 
-namespace {
-
-struct TuneEntry {
-  int dtype;
-  int size_class;
-  LaunchCfg cfg;
-};
-
-}  // namespace
-
 struct s3a_handle {
   int device = 0;
   int n_cu = 256;
@@ -36,7 +26,7 @@ struct s3a_handle {
   Work w{};
   bool forced[2] = {false, false};
   LaunchCfg forced_cfg[2];
-  std::vector<TuneEntry> tuned;
+  TuneTable tuned;
   PgoWorkspace* pgo = nullptr;
   CallDesc* desc = nullptr;
   bool timing = false;
@@ -194,15 +184,6 @@ int check_desc(const s3a_align_desc* d) {
   return S3A_OK;
 }
 
-int size_class(int64_t n_points) {
-  int c = 0;
-  while (n_points > 65536 && c < 12) {
-    n_points >>= 2;
-    ++c;
-  }
-  return c;
-}
-
 // Untuned shapes: one workgroup per tile, which the hardware hands out as others
 // end (four a compute unit looping over the tiles left the last round ragged: 256
 // pairs of 32 M points 1607 us a call against 1546, BF16 959 against 870, the cost
@@ -217,24 +198,16 @@ LaunchCfg default_cfg(int dtype) {
   return c;
 }
 
-// A forced shape applies to plane and depth-map input of its plane type; tuned
-// shapes are kept per input kind (plane or depth map, FP32 or BF16) and size
-// class.
-LaunchCfg pick_cfg(s3a_handle* h, int dtype, int64_t n_points) {
-  if (h->forced[dtype & 1]) return h->forced_cfg[dtype & 1];
-  const int sc = size_class(n_points);
-  for (auto& t : h->tuned)
-    if (t.dtype == dtype && t.size_class == sc) return t.cfg;
-  return default_cfg(dtype);
-}
-
-// A shape was forced or tuned for calls of this kind and size class.
-bool has_cfg(s3a_handle* h, int dtype, int64_t n_points) {
-  if (h->forced[dtype & 1]) return true;
-  const int sc = size_class(n_points);
-  for (auto& t : h->tuned)
-    if (t.dtype == dtype && t.size_class == sc) return true;
-  return false;
+// A call's shape, and whether it is the untuned one. A forced shape applies to plane and
+// depth-map input of its plane type; tuned shapes are kept per kind of call (TuneTable).
+struct Picked {
+  LaunchCfg cfg;
+  bool untuned;
+};
+Picked pick_cfg(s3a_handle* h, int dtype, int64_t n_points, int n_pairs, bool persistent, bool solving) {
+  if (h->forced[dtype & 1]) return {h->forced_cfg[dtype & 1], false};
+  const LaunchCfg* c = h->tuned.find(dtype, n_points, n_pairs, persistent, solving);
+  return c ? Picked{*c, false} : Picked{default_cfg(dtype), true};
 }
 
 bool valid_cfg(const LaunchCfg& c) {
@@ -253,7 +226,7 @@ Shape make_shape(const s3a_align_desc* d, const LaunchCfg& lc) {
   sh.delta_f = (float)d->huber_delta;
   sh.flags = d->flags;
   sh.tile_elems = (int32_t)tile_elems(d->dtype, lc);
-  sh.vec = (d->dtype & 1) ? 8 : 4;
+  sh.vec = vec_of(d->dtype);
   return sh;
 }
 
@@ -310,9 +283,12 @@ hipError_t enqueue_batched(s3a_handle* h, int dtype, const LaunchCfg& lc, const 
 // tiles) 289 -> 294; depth frames of 203,056 pixels, 4 pairs 217 -> 199, 20 pairs (260
 // tiles) 269 -> 250, 60 pairs (780 tiles) 423 -> 418, BF16 32 pairs 314 -> 288, 100
 // pairs (700 tiles) 596 -> 589. A pair of many tiles pays for the gather: one pair of
-// 2 M points (490 tiles) 208 -> 186, of 4 M 329 -> 350.
-bool passes_solve(s3a_handle* h, int dtype, int64_t n_points, int n_pairs, int64_t tiles) {
-  return !has_cfg(h, dtype, n_points) && tiles <= 4 * (int64_t)h->n_cu && tiles <= 512 * (int64_t)n_pairs;
+// 2 M points (490 tiles) 208 -> 186, of 4 M 329 -> 350. The host does not know the
+// largest pair, so a batch of one such and small ones pays too: with 30 pairs of
+// 2,000 points, a pair of 500 tiles 225 -> 191, of 700 279 -> 248, of 900 332 -> 346.
+bool passes_solve(const s3a_handle* h, int dtype, int64_t n_points, int n_pairs) {
+  const int64_t tiles = max_tiles(n_points, n_pairs, tile_elems(dtype, default_cfg(dtype)));
+  return tiles <= 4 * (int64_t)h->n_cu && tiles <= 512 * (int64_t)n_pairs;
 }
 
 hipError_t enqueue_solving(s3a_handle* h, int dtype, const LaunchCfg& lc, const Shape& sh, const CallDesc* dcd,
@@ -413,7 +389,10 @@ int align_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_pair* dept
   DeviceGuard g(h->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
   S3A_ORDERED(h, st);
-  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
+  const bool plain = (d->flags & S3A_FLAG_PLAIN) != 0, persistent = !plain && (d->flags & S3A_FLAG_PERSISTENT);
+  const bool can_solve = !plain && !persistent && passes_solve(h, d->dtype, d->n_points, d->n_pairs);
+  const Picked pick = pick_cfg(h, d->dtype, d->n_points, d->n_pairs, persistent, can_solve);
+  const LaunchCfg& lc = pick.cfg;
   const Shape sh = make_shape(d, lc);
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
   if (mt >= (1ll << 31)) return S3A_EINVAL;
@@ -426,7 +405,7 @@ int align_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_pair* dept
   c.depth = depth;
   CallDesc* dcd = desc_slot(h);
 
-  if (d->flags & S3A_FLAG_PLAIN) {
+  if (plain) {
     // one pair at a time: read the schedule back, then 1 + K (+1) passes per pair
     S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
     std::vector<PairSched> sched(d->n_pairs);
@@ -448,9 +427,9 @@ int align_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_pair* dept
   }
 
   S3A_TRY(launch_sched(sh, c, dcd, h->w, st));
-  if (d->flags & S3A_FLAG_PERSISTENT)
+  if (persistent)
     S3A_TRY(enqueue_persistent(h, d->dtype, lc, sh, dcd, st));
-  else if (passes_solve(h, d->dtype, d->n_points, d->n_pairs, mt))
+  else if (can_solve && pick.untuned)
     S3A_TRY(enqueue_solving(h, d->dtype, lc, sh, dcd, (int)mt, st));
   else
     S3A_TRY(enqueue_batched(h, d->dtype, lc, sh, dcd, st));
@@ -634,7 +613,7 @@ int s3a_align_cost(s3a_handle* h, const s3a_align_desc* d, const s3a_sim3* S, co
   DeviceGuard g(h->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
   S3A_ORDERED(h, st);
-  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
+  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points, d->n_pairs, false, false).cfg;
   const Shape sh = make_shape(d, lc);
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
   if (mt >= (1ll << 31)) return S3A_EINVAL;
@@ -677,7 +656,7 @@ static int backward_impl(s3a_handle* h, bool zero_rest, const s3a_align_desc* d,
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (d->n_pairs == 0) return zero_rest ? zero_planes(h, gr, d->n_points, st) : S3A_OK;
   S3A_ORDERED(h, st);
-  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
+  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points, d->n_pairs, false, false).cfg;
   Shape sh = make_shape(d, lc);
   if (zero_rest) sh.flags |= SHAPE_ZERO_REST;
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
@@ -718,7 +697,7 @@ static int implicit_backward_impl(s3a_handle* h, bool zero_rest, const s3a_align
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (d->n_pairs == 0) return zero_rest ? zero_planes(h, gr, d->n_points, st) : S3A_OK;
   S3A_ORDERED(h, st);
-  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points);
+  const LaunchCfg lc = pick_cfg(h, d->dtype, d->n_points, d->n_pairs, false, false).cfg;
   Shape sh = make_shape(d, lc);
   if (zero_rest) sh.flags |= SHAPE_ZERO_REST;
   const int64_t mt = max_tiles(sh.n_points, sh.n_pairs, sh.tile_elems);
@@ -819,7 +798,8 @@ int s3a_set_tuning(s3a_handle* h, int32_t dtype, const s3a_tuning* t) {
 
 int s3a_get_tuning(s3a_handle* h, int32_t dtype, int64_t n_points, s3a_tuning* t) {
   if (!h || !t || (dtype != S3A_F32 && dtype != S3A_BF16)) return S3A_EINVAL;
-  const LaunchCfg c = pick_cfg(h, dtype, n_points);
+  const LaunchCfg* tuned = h->tuned.last(dtype, n_points);
+  const LaunchCfg c = h->forced[dtype & 1] ? h->forced_cfg[dtype & 1] : tuned ? *tuned : default_cfg(dtype);
   t->wg = c.wg;
   t->items = c.items;
   t->occupancy = c.occupancy;
@@ -875,10 +855,7 @@ static int autotune_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_
   };
   // an untuned call may solve in its passes, which no tuned shape does: it is kept
   // unless a shape is faster
-  const int sc = size_class(d->n_points);
-  h->tuned.erase(std::remove_if(h->tuned.begin(), h->tuned.end(),
-                                [&](const TuneEntry& t) { return t.dtype == d->dtype && t.size_class == sc; }),
-                 h->tuned.end());
+  h->tuned.record(d->dtype, d->n_points, d->n_pairs, persistent, nullptr);
   h->forced[plane] = false;
   float best_ms = timed();
   bool shaped = false;
@@ -906,7 +883,7 @@ static int autotune_run(s3a_handle* h, const s3a_align_desc* d, const s3a_depth_
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   (void)hipFree(S);
-  if (shaped) h->tuned.push_back(TuneEntry{d->dtype, sc, bestc});
+  if (shaped) h->tuned.record(d->dtype, d->n_points, d->n_pairs, persistent, &bestc);
   if (best) {
     best->wg = bestc.wg;
     best->items = bestc.items;

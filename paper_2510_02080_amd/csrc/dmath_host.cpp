@@ -1,7 +1,9 @@
 // Host build of the FP64 per-pair / per-edge math that the kernels run on the
-// device, exported with C linkage so it can be checked on a machine without a
-// GPU. Internal test hooks; not part of the public interface.
+// device, and of the rule that picks a call's launch shape, exported with C
+// linkage so they can be checked on a machine without a GPU. Internal test
+// hooks; not part of the public interface.
 #include "dmath.h"
+#include "tuning.h"
 
 using namespace s3a;
 
@@ -65,4 +67,22 @@ int s3a_host_umeyama(const double* m, double* T) {
 void s3a_host_rotation_from_cross_cov(const double* M, double* R) { rotation_from_cross_cov(M, R); }
 
 void s3a_host_singular_values3(const double* M, double* sv) { singular_values3(M, sv); }
+
+void* s3a_host_tune_new() { return new TuneTable(); }
+void s3a_host_tune_free(void* t) { delete static_cast<TuneTable*>(t); }
+// wg 0: the untuned call was fastest
+void s3a_host_tune_record(void* t, int dtype, long long n_points, long long n_pairs, int persistent, int wg) {
+  LaunchCfg c;
+  c.wg = wg;
+  static_cast<TuneTable*>(t)->record(dtype, n_points, n_pairs, persistent != 0, wg ? &c : nullptr);
+}
+// the shape's wg, 0: untuned
+int s3a_host_tune_find(void* t, int dtype, long long n_points, long long n_pairs, int persistent, int solving) {
+  const LaunchCfg* c = static_cast<TuneTable*>(t)->find(dtype, n_points, n_pairs, persistent != 0, solving != 0);
+  return c ? c->wg : 0;
+}
+int s3a_host_tune_last(void* t, int dtype, long long n_points) {
+  const LaunchCfg* c = static_cast<TuneTable*>(t)->last(dtype, n_points);
+  return c ? c->wg : 0;
+}
 }
