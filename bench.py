@@ -283,7 +283,7 @@ def main():
         verp = dict(ver, bitwise_equal_to="batched_fp32") if (same and ver is not None) else verify("cfg2", Sp, ibp)
         res["persistent_fp32"] = dict(ms_per_step=ms_p, kernel_ms=kp,
                                       points_per_s=counted_points(verp, V_total) / (ms_p / 1e3),
-                                      vs_graph_path=ms / ms_p, bitwise_equal_graph_path=same, tuning=tune_p,
+                                      vs_per_pass=ms / ms_p, bitwise_equal_per_pass=same, tuning=tune_p,
                                       verify=verp)
         log(f"persistent fp32: {ms_p:.3f} ms/step (kernel {kp:.3f} ms, shape {tune_p}), per-pass launches {ms:.3f} ms, "
             f"bitwise equal {same}")

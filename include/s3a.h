@@ -32,7 +32,8 @@
  *     stream) and return; device outputs are valid once the stream has
  *     reached that point. Calls that say they synchronise do so on that
  *     stream before returning.
- *   - A handle owns its workspace (grown on demand) and autotuning results. A handle must not be used by two threads at once.
+ *   - A handle owns its workspace (grown on demand) and autotuning results. A
+ *     handle must not be used by two threads at once.
  *   - Calls through one handle share that workspace, so they execute in the
  *     order they were issued, whatever streams they are given: a call on a
  *     stream other than the previous call's makes its stream wait (on the
@@ -454,10 +455,12 @@ int s3a_set_tuning(s3a_handle* h, int32_t dtype, const s3a_tuning* t); /* t = NU
 int s3a_get_tuning(s3a_handle* h, int32_t dtype, int64_t n_points, s3a_tuning* t);
 
 /*
- * Kernel timing (profiling aid). While on, calls record HIP events on the caller's stream around every launch of
- * the call's dominant point kernel: the persistent kernel of a batched call,
- * the pass kernels of a plain or multi-launch call, the adjoint kernel of a
- * backward call, the cost kernel of a cost call. s3a_kernel_time synchronises
+ * Kernel timing (profiling aid). While on, calls record HIP events on the
+ * caller's stream around every launch of the call's dominant point kernel: the
+ * persistent kernel of a batched call, the pass kernels of a plain or
+ * multi-launch call (in small untuned calls these include the solve of the pass
+ * before, but not the last solve), the adjoint kernel of a backward call, the
+ * cost kernel of a cost call. s3a_kernel_time synchronises
  * on those events and returns their summed duration (ms) and launch count
  * since the previous s3a_kernel_time, then clears them.
  */

@@ -144,9 +144,9 @@ class Pointmaps:
     torch.bfloat16 tensors) plus int64 offsets[n_pairs + 1]."""
 
     def __init__(self, planes, offsets, dtype, covers_all=False):
-        """covers_all: the caller asserts that the offsets are non-decreasing
-        from 0 to N (every stored point belongs to a pair). The gradient
-        calls no longer need to know: they write zeros outside the pairs."""
+        """covers_all (the offsets are non-decreasing from 0 to N, so that every
+        stored point belongs to a pair) is accepted and kept as an attribute;
+        nothing in this package depends on it."""
         assert len(planes) == 7
         self.planes = list(planes)
         self.offsets = offsets

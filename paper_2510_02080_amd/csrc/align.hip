@@ -288,7 +288,7 @@ __device__ inline bool solve_pass(const Shape& sh, const CallDesc* __restrict__ 
 // system itself, while its own first loads are in flight, so the launch between two
 // passes is gone. A call of few tiles is bound by that chain alone: pass 5.0 +
 // finalize 5.0 us for one pair of 3,072 points. With more tiles than the chip holds
-// at once the repeated solves cost more than the launch (see solve_tiles).
+// at once the repeated solves cost more than the launch (see passes_solve).
 // FIRST: the solve is the closed form's (pass 1), which takes registers that the
 // later passes' kernels then need not hold: three of those share a SIMD.
 template <int DT, int MODE, int WG, int ITEMS, bool FIRST>

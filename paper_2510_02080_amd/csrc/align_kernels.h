@@ -332,8 +332,8 @@ __device__ inline int tile_lo(const TileDesc& td) { return td.lo > td.begin ? (i
 // Depth input: three planes (d_p, d_q, c), the pixel's frame, row and column
 // from its index in the pair, and each side unprojected with its camera:
 // x = R (d ((col, row) * inv_f + o, 1)) + t. Elements before the pair's start
-// (the head of a boundary vector) get the pair's first pixel; the tile bodies
-// zero them anyway.
+// (the head of a boundary vector) count back from its first pixel; the tile bodies
+// mask them.
 __device__ inline DepthCam load_cam_uniform(const DepthCam* c) {
   DepthCam r;
   r.ifx = uniform_f32(c->ifx);

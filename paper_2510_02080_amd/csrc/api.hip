@@ -155,7 +155,6 @@ int ensure_workspace(s3a_handle* h, int n_pairs, int64_t tiles) {
   h->w.counters = reinterpret_cast<uint32_t*>(b + o_cnt);
   h->w.flags = reinterpret_cast<uint32_t*>(b + o_flag);
   h->w.total_tiles = reinterpret_cast<int32_t*>(b + o_tot);
-  h->w.scan_tmp = nullptr;
   h->w.tiles_cap = nt;
   h->w.pairs_cap = np;
   h->desc = reinterpret_cast<CallDesc*>(b + o_desc);
@@ -526,7 +525,6 @@ int s3a_align_pairs_noalloc(const s3a_align_desc* d, const s3a_sim3* init, s3a_s
   w.total_tiles = reinterpret_cast<int32_t*>(base + NA_O_TOTAL);
   w.counters = nullptr;  // persistent launch only
   w.flags = nullptr;
-  w.scan_tmp = nullptr;
   w.dpairs = nullptr;    // depth input only
   CallDesc c = make_call(d);
   c.init = init;

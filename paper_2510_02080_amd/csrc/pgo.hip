@@ -107,7 +107,7 @@ struct PgoDev {
   // breadth-first depth levels of the chain: entries [chain_lev[l], chain_lev[l+1]) have depth l + 1
   const int32_t* chain_lev; int32_t n_chain_lev;
   // numeric storage
-  double* Ld;     // [m][49] diagonal blocks (lower Cholesky factor after factorisation)
+  double* Ld;     // [m][49] diagonal blocks, updated in place; their factors are kept as inverses only
   double* Di;     // [m][49] inverses of the factored diagonal blocks of the sparse columns
   double* Lb;     // [nblk][49]
   double* g;      // [m][7]  gradient, then solution

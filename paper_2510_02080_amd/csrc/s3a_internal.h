@@ -166,7 +166,6 @@ struct Work {
   int32_t* total_tiles;
   uint32_t* counters;  // [n_pairs] arrivals, then 4 scheduling words
   uint32_t* flags;     // [n_pairs] per-pair published pass (persistent launch)
-  int32_t* scan_tmp;
   DepthPair* dpairs;   // [n_pairs] cameras in pass form (depth input)
 };
 
