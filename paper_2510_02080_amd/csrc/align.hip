@@ -76,6 +76,7 @@ __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, 
   t.tile0 = tile0;
   t.ntiles = ntiles;
   t.frame = -1;
+  t.head = j == 0 ? (int16_t)(a - b0) : (int16_t)0;
   if (b > a) {
     t.begin = b0 + (int64_t)j * T;
     t.end = t.begin + T < b ? t.begin + T : b;
@@ -86,10 +87,11 @@ __device__ inline TileDesc make_tile(int64_t a, int64_t b, int pair, int tile0, 
       const int rows = depth->frame_pixels / depth->width;
       if (f0 == f1 && f0 < depth->n_frames && f0 < DEPTH_MAX_FRAMES && t.end > first &&
           camera_plain(depth->p[f0], depth->width, rows) && camera_plain(depth->q[f0], depth->width, rows))
-        t.frame = f0;
+        t.frame = (int16_t)f0;
     }
   } else {
     t.begin = t.end = t.lo = a;
+    t.head = 0;
   }
   return t;
 }

@@ -10,6 +10,8 @@
 // bitwise reproducible run to run.
 #pragma once
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "s3a_internal.h"
@@ -322,12 +324,14 @@ __device__ inline TileDesc load_tile(const TileDesc* p) {
   r.pair = uniform_i32(p->pair);
   r.tile0 = uniform_i32(p->tile0);
   r.ntiles = uniform_i32(p->ntiles);
-  r.frame = uniform_i32(p->frame);
+  static_assert(offsetof(TileDesc, head) == offsetof(TileDesc, frame) + 2, "read as one word");
+  int at;
+  __builtin_memcpy(&at, &p->frame, sizeof(at));
+  at = uniform_i32(at);
+  r.frame = (int16_t)at;
+  r.head = (int16_t)(at >> 16);
   return r;
 }
-
-// Where a tile's pair starts in it (past its head in the pair's first tile; else 0).
-__device__ inline int tile_lo(const TileDesc& td) { return td.lo > td.begin ? (int)(td.lo - td.begin) : 0; }
 
 // Depth input: three planes (d_p, d_q, c), the pixel's frame, row and column
 // from its index in the pair, and each side unprojected with its camera:
@@ -747,7 +751,7 @@ template <int DT, int WG, int ITEMS, typename Point>
 __device__ inline void span_walk(const Shape& sh, const SrcCtx<DT>& s, const TileDesc& td, Point&& point) {
   using L = DepthPlanes<DT>;
   constexpr int VEC = L::VEC, STRIDE = WG * VEC;
-  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
   const int64_t at = td.begin - s.a;
   int seg = lo_rel > 0 ? lo_rel : 0;
 #pragma unroll 1
@@ -845,7 +849,7 @@ __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& sr
   }
   const float tau = sh.tau, delta = sh.delta_f;
   const float d2 = delta * delta, hd2 = 0.5f * delta * delta;
-  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
   const bool check_finite = P.mask != MASK_NONE;
   auto fetch = [&](int rel, typename L::Raw& r) { L::fetch(src, td.begin + rel, sh.n_points, r); };
   DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
@@ -977,7 +981,7 @@ __device__ inline void tile_gn(const Shape& sh, const SrcCtx<DT>& pl, const Tile
     }
   }
   if (P.active) {
-    const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+    const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
     const bool check_finite = P.mask != MASK_NONE, check_extreme = P.mask == MASK_EXTREME;
     if constexpr (DT == S3A_F32 || DT == S3A_BF16) {
       auto fetch = [&](int rel, RawVec& r) { Planes<DT>::fetch(pl, td.begin + rel, sh.n_points, r); };
@@ -1022,7 +1026,7 @@ __device__ inline void tile_moments_depth_frame(const Shape& sh, const SrcCtx<DT
   const DepthCam& cp = src.cp;
   const DepthCam& cq = src.cq;
   const float tau = sh.tau;
-  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
   DepthWalk<DT> pos(src, td, (int)threadIdx.x * VEC, WG * VEC);
   const CamForm fp(cp.R, cp), fq(cq.R, cq);
   auto body = [&](const typename L::Raw& raw, int rel0) {
@@ -1100,7 +1104,7 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
   for (int j = 0; j < NSTAT; ++j) a[j] = 0.0;
   int nvalid = 0, nbad = 0;
   const float tau = sh.tau;
-  const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+  const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
   if constexpr (DT == DT_DEPTH_F32 || DT == DT_DEPTH_BF16) {
     if (pl.frame >= 0) {
       tile_moments_depth_frame<DT, WG, ITEMS, BEGUN>(sh, pl, td, first, a, nvalid, nbad, extreme);
@@ -1160,7 +1164,7 @@ __device__ inline void tile_cost(const Shape& sh, const SrcCtx<DT>& pl, const Ti
   constexpr int VEC = Planes<DT>::VEC;
   double acc[3] = {0.0, 0.0, 0.0};
   if (P.active) {
-    const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+    const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
 #pragma unroll 1
     for (int it = 0; it < ITEMS; ++it) {
       const int rel0 = (it * WG + (int)threadIdx.x) * VEC;

@@ -445,7 +445,7 @@ __global__ __launch_bounds__(WG) void k_igrad(Shape sh, const CallDesc* __restri
 #pragma unroll
     for (int i = 0; i < 7; ++i) vv[i] = S->g[i];
     const double vF = S->cost_lin, iC = P.active ? 1.0 / S->C : 0.0;
-    const int lo_rel = tile_lo(td), end_rel = (int)(td.end - td.begin);
+    const int lo_rel = td.head, end_rel = (int)(td.end - td.begin);
 #pragma unroll 1
     for (int it = 0; it < ITEMS; ++it) {
       const int rel0 = (it * WG + (int)threadIdx.x) * VEC;

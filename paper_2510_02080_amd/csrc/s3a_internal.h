@@ -67,7 +67,8 @@ struct TileDesc {
   int32_t pair;
   int32_t tile0;  // the pair's first tile and tile count (PairSched's, beside the tile
   int32_t ntiles; // so that a pass needs one load before it can issue the others)
-  int32_t frame;  // depth input: the frame the tile lies in, -1 when it spans frames
+  int16_t frame;  // depth input: the frame the tile lies in, -1 when it spans frames
+  int16_t head;   // where the pair starts in the tile (in its first one, below TILE_ALIGN; else 0)
 };
 
 struct PairSched {
