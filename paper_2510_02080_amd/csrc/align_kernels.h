@@ -259,7 +259,7 @@ __device__ inline float max3_abs(float x, float y, float z) { return fmaxf(fmaxf
 // Whether a lane of a moments pass has met a point whose largest value `size` (NaN
 // apart) lies in [from, infinity): the bits of such a size, less from's, are the
 // small unsigned numbers, whose least is kept. (Counted by masks instead, the moments of
-// 256 depth pairs took 225 us, and 211 with all coordinates looked at; 186 without.)
+// 256 depth pairs took 225 us against 187.)
 struct ExtremeSeen {
   float from;
   uint32_t least = ~0u;
@@ -828,7 +828,8 @@ __device__ inline void tile_begin(const Shape& sh, const void* const* pl, const 
 // cycles each on a SIMD, are 1.7 us a million pixels for the chip at its clock, and
 // the loads alone as long. Forming a row's share of the ray, the positions and the
 // masks once a vector, and the fourth wavefront per SIMD that the saved registers give:
-// 256 pairs of 518 x 392 frames (62 M pixels) 169 -> 159 us a pass; a few pairs, bound
+// 256 pairs of 518 x 392 frames (62 M pixels) 169 -> 159 us a pass (140
+// since extreme pairs have a walk of their own, by the registers it leaves); a few pairs, bound
 // by one wavefront's chain, 345 -> 200 us a call of 10 steps.
 template <int DT, int WG, int ITEMS, bool COST, bool BEGUN>
 __device__ inline void tile_gn_depth_frame(const Shape& sh, const SrcCtx<DT>& src, const TileDesc& td,
@@ -1115,13 +1116,21 @@ __device__ inline void tile_moments(const Shape& sh, const SrcCtx<DT>& pl, const
       return;
     }
   }
-  // one point: validity (counted), then the weighted raw moments in FP64
+  // one point: validity (counted), then the weighted raw moments in FP64. The largest
+  // coordinate tells infinities too, and a comparison a NaN in either of two, which pays for
+  // looking at it (32 M BF16 points, the closed form alone: a class test per value 113 us
+  // a call, with the largest beside it 120, this 110).
   auto point = [&](float (&x)[7], bool in) {
-    const bool fin = finite7(x);
+    const float size = fmaxf(max3_abs(x[0], x[1], x[2]), max3_abs(x[3], x[4], x[5]));  // NaN apart
+    const bool nans =
+        __builtin_isunordered(x[0], x[1]) | __builtin_isunordered(x[2], x[3]) | __builtin_isunordered(x[4], x[5]);
+    const bool fin = !nans & (size < __builtin_inff()) & __builtin_isfinite(x[6]);
     const bool valid = in && fin && x[6] >= tau;
     nvalid += valid ? 1 : 0;
     nbad += (in && !fin) ? 1 : 0;
-    extreme.look(in, fmaxf(max3_abs(x[0], x[1], x[2]), max3_abs(x[3], x[4], x[5])));
+    // (a neighbour's element in a vector of stored points may be seen too: the masks it
+    // brings change no sum)
+    extreme.look(in || DT == S3A_F32 || DT == S3A_BF16, size);
 #pragma unroll
     for (int j = 0; j < 7; ++j) x[j] = valid ? x[j] : 0.0f;
     const double w = x[6];
