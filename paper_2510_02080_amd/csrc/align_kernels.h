@@ -824,9 +824,9 @@ __device__ inline void tile_begin(const Shape& sh, const void* const* pl, const 
 // current similarity is folded into each side's camera once per tile, so a
 // pixel costs one affine map per side on its ray:
 //   y_c = d_p (A ray_p) + b,  A = sR R_p, b = sR t_p + t - c;   q_c = d_q (R_q ray_q) + t_q - c.
-// Bound by instruction issue, not by the loads: about 71 vector operations a pixel, four
-// cycles each on a SIMD, are 1.7 us a million pixels for the chip at its clock, and
-// the loads alone as long. Forming a row's share of the ray, the positions and the
+// Bound by instruction issue, not by the loads: 65 vector operations a pixel in the compiled
+// loop, 71 where a row ends in the vector, four cycles each on a SIMD, are 1.6 to 1.7 us a
+// million pixels for the chip at its clock, and the loads alone as long. Forming a row's share of the ray, the positions and the
 // masks once a vector, and the fourth wavefront per SIMD that the saved registers give:
 // 256 pairs of 518 x 392 frames (62 M pixels) 169 -> 159 us a pass (140
 // since extreme pairs have a walk of their own, by the registers it leaves); a few pairs, bound
